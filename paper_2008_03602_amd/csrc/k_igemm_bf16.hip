@@ -37,7 +37,6 @@ struct IgBf16Args {
 };
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 template <int MF>
 struct MfmaBf16;

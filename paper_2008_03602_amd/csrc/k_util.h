@@ -27,6 +27,26 @@ __device__ __forceinline__ float bload1(__amdgpu_buffer_rsrc_t r, int off) {
   return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
 }
 
+typedef unsigned int u32x3 __attribute__((ext_vector_type(3)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+// Three consecutive words at byte offset off (a multiple of 4) of r.
+__device__ __forceinline__ void bload3(__amdgpu_buffer_rsrc_t r, int off, float* v) {
+  const u32x3 q = __builtin_amdgcn_raw_buffer_load_b96(r, off, 0, 0);
+  const unsigned a = q.x, b = q.y, c = q.z;
+  v[0] = __builtin_bit_cast(float, a);
+  v[1] = __builtin_bit_cast(float, b);
+  v[2] = __builtin_bit_cast(float, c);
+}
+__device__ __forceinline__ void bstore1(__amdgpu_buffer_rsrc_t r, int off, float v) {
+  __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, off, 0, 0);
+}
+
+// Offsets that are sums of up to three parts (plane, row, column), each of which may be
+// out of range on its own: buffers of at most kPartOob bytes, and kPartOob for a part
+// outside. Any sum with such a part is then past the buffer, and three of them (plus an
+// instruction's immediate) stay below 2^32.
+constexpr int kPartOob = 0x3FFFFFF0;
+
 typedef __attribute__((address_space(3))) void lds_void_t;
 // One wave instruction: lane i copies the word at byte offset off of r to
 // lds[i] (an inactive lane copies nothing), without a trip through registers.
@@ -44,6 +64,24 @@ __device__ __forceinline__ void wait_copies() { asm volatile("s_waitcnt vmcnt(0)
 // floor(n / d) for 0 <= n < 2^22 given inv = 1/d in fp32: (n + 1/2)/d lies at
 // least 1/(2d) from an integer and the fp32 product errs by less than that.
 __device__ __forceinline__ int qdiv(int n, float inv) { return (int)(((float)n + 0.5f) * inv); }
+
+// floor(n / d) for 0 <= n < 2^31 with a host-computed multiplier: m = ceil(2^(31+s) / d)
+// for the smallest 2^s >= d, so m * d exceeds 2^(31+s) by less than 2^s and n times that
+// excess stays below 2^(31+s). On a uniform n this is two scalar multiplies.
+struct FastDiv {
+  uint32_t m;
+  int32_t sh;  // 31 + s
+  int32_t d;
+};
+inline FastDiv make_fastdiv(int64_t d) {
+  int s = 0;
+  while (((int64_t)1 << s) < d) ++s;
+  const uint64_t p = (uint64_t)1 << (31 + s);
+  return {(uint32_t)((p + (uint64_t)d - 1) / (uint64_t)d), 31 + s, (int32_t)d};
+}
+__host__ __device__ __forceinline__ int fdiv(int n, const FastDiv& f) {
+  return (int)(((uint64_t)(uint32_t)n * f.m) >> f.sh);
+}
 
 // Block renumbering for XCD locality: the device deals consecutive blocks to
 // its 8 XCDs in turn, so block b runs on XCD b mod 8. Tile of block b when

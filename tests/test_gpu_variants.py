@@ -1,0 +1,73 @@
+"""GPU parity at the edges of the kernels' own choices of path: sizes where an index, a
+load width or an address range changes, against the fp64 oracle (or, for tensors too large
+for it, against shifted sums in torch)."""
+import random
+
+import pytest
+import torch
+
+from paper_2008_03602_amd import _lib as L, workloads as W
+from gpu_util import check_close, device_ready, make_inputs, note, reference, sched_str, to_device
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _device():
+    device_ready()
+    yield
+
+
+def _dw(name, n, c, h, w, r, s, stride, pad):
+    return W.Op(name, n, c, h, w, c, r, s, stride, stride, pad[0], pad[1], 1, 1, c, 0, 0)
+
+
+# one-row and one-column maps, channel and image groups that run past the tensor, a
+# rectangular filter and a stride the fixed paths do not take
+DW_EDGES = [
+    _dw("row", 3, 5, 1, 9, 3, 3, 1, (1, 1)),
+    _dw("column", 2, 17, 9, 1, 3, 3, 2, (1, 1)),
+    _dw("wide33", 5, 6, 6, 33, 3, 3, 1, (1, 1)),
+    _dw("s2_31", 3, 3, 31, 30, 3, 3, 2, (1, 1)),
+    _dw("rect1x5", 2, 9, 8, 13, 1, 5, 1, (0, 2)),
+    _dw("stride3", 1, 4, 16, 16, 3, 3, 3, (1, 1)),
+]
+
+
+@pytest.mark.parametrize("op", DW_EDGES, ids=lambda o: o.name)
+def test_depthwise_edges_match_oracle(op):
+    x, w = make_inputs(op, "uniform", seed=41)
+    ref, a = reference(op, x, w)
+    xd, wd, yd = to_device(op, x, w)
+    space = L.ct_valid_space(op)
+    for s in random.Random(6).sample(space, min(48, len(space))):
+        tag = "%s %s" % (op.name, sched_str(s))
+        note(tag)
+        yd.fill_(float("nan"))
+        L.conv2d_run(op, s, xd, wd, yd)
+        check_close(op, yd.cpu().numpy(), ref, a, tag)
+
+
+def test_depthwise_planes_beyond_the_32_bit_part_offsets():
+    # two planes of 512 MB + : a block's planes span more than 2^30 bytes
+    op = _dw("huge", 1, 2, 8200, 16400, 3, 3, 1, (1, 1))
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(7)
+    xd = torch.rand(op.x_shape(), generator=gen, device="cuda") * 2 - 1
+    wd = torch.rand(op.w_shape(), generator=gen, device="cuda") * 2 - 1
+    ref = torch.zeros(op.y_shape(), device="cuda")
+    p = torch.nn.functional.pad(xd, (1, 1, 1, 1))
+    for r in range(3):
+        for s in range(3):
+            ref += p[:, :, r:r + op.h, s:s + op.w] * wd[:, :, r, s].reshape(1, -1, 1, 1)
+    del p
+    yd = torch.empty(op.y_shape(), device="cuda")
+    for lds in (0, 1):
+        s = L.make_schedule(W.FAM_DEPTHWISE_F32, (2, 8, 64, 2, 2, lds, 1, 0, 0))
+        assert L.ct_validate(op, s) == L.S_OK
+        note("huge " + sched_str(s))
+        yd.fill_(float("nan"))
+        torch.cuda.synchronize()
+        L.conv2d_run(op, s, xd, wd, yd)
+        # 9 products of at most 1: both sums err by at most 9 roundings of at most 9 * 2^-24
+        assert float((yd - ref).abs().max()) <= 2 * 9 * 9 * 2.0 ** -24
