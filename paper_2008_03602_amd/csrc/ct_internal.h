@@ -63,7 +63,17 @@ namespace bf16_knob { enum { MF, TM, TN, WM, WN, KC, LDS, SPLIT, SWZ, COUNT }; }
 namespace f32g_knob { enum { MF, TM, TN, WM, WN, WS, TPW, CPC, STAGES, SPLIT, COUNT }; }
 
 // Filter/stride specialisation chosen from the op (not a knob).
-enum Spec { SPEC_GENERIC = 0, SPEC_1X1_S1 = 1, SPEC_1X1_S2 = 2, SPEC_3X3_S1 = 3, SPEC_3X3_S2 = 4 };
+// The ROW ones (filters of 5 or 7 columns, column stride 1 or 2, no column
+// dilation) are the direct family's.
+enum Spec {
+  SPEC_GENERIC = 0, SPEC_1X1_S1 = 1, SPEC_1X1_S2 = 2, SPEC_3X3_S1 = 3, SPEC_3X3_S2 = 4,
+  SPEC_ROW5_S1 = 5, SPEC_ROW5_S2 = 6, SPEC_ROW7_S1 = 7, SPEC_ROW7_S2 = 8
+};
+// Columns of the filter and column stride of a direct specialisation (0: runtime).
+constexpr int direct_spec_s(int spec) {
+  return spec == 0 ? 0 : (spec <= 2 ? 1 : (spec <= 4 ? 3 : (spec <= 6 ? 5 : 7)));
+}
+constexpr int direct_spec_stride(int spec) { return spec == 0 ? 0 : (spec % 2 ? 1 : 2); }
 Spec op_spec(const OpX& x);
 
 struct Geom {
@@ -78,6 +88,8 @@ struct Geom {
   // family-specific derived values
   int64_t tiles_h, tiles_w, tiles_k, tiles_c, tiles_n;  // grid factors
   int ih_t, iw_t;     // input halo tile (direct, depthwise)
+  int d_alt;          // direct family: the ALT variant (k_direct.inc.h)
+  int d_pitch, d_wpc, d_ks, d_wt;  // direct family, LDS words: halo row; filter per output channel, per group of MK, all
   int bm, bn;         // GEMM block tile (rows x cols)
   int chunks;         // reduction chunks in total
   int chunks_per_split;

@@ -2,5 +2,5 @@
 #include "k_direct.inc.h"
 
 namespace ct {
-DirectFn pick_direct_mk1(int mw, int lds, int spec, int unr) { return pick_mw<1>(mw, lds, spec, unr); }
+DirectFn pick_direct_mk1(int mw, int lds, int spec, int unr, bool alt) { return pick_mw<1>(mw, lds, spec, unr, alt); }
 }  // namespace ct

@@ -27,6 +27,7 @@ __device__ __forceinline__ float bload1(__amdgpu_buffer_rsrc_t r, int off) {
   return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
 }
 
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x3 __attribute__((ext_vector_type(3)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 // Three consecutive words at byte offset off (a multiple of 4) of r.
@@ -36,6 +37,29 @@ __device__ __forceinline__ void bload3(__amdgpu_buffer_rsrc_t r, int off, float*
   v[0] = __builtin_bit_cast(float, a);
   v[1] = __builtin_bit_cast(float, b);
   v[2] = __builtin_bit_cast(float, c);
+}
+// N consecutive words at byte offset off (a multiple of 4) of r, in loads of up to four
+// words; words past the buffer's range read 0.
+template <int N>
+__device__ __forceinline__ void bload_words(__amdgpu_buffer_rsrc_t r, int off, float* v) {
+  if constexpr (N >= 4) {
+    const u32x4 q = __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0);
+    const unsigned a = q.x, b = q.y, c = q.z, d = q.w;
+    v[0] = __builtin_bit_cast(float, a);
+    v[1] = __builtin_bit_cast(float, b);
+    v[2] = __builtin_bit_cast(float, c);
+    v[3] = __builtin_bit_cast(float, d);
+    bload_words<N - 4>(r, off + 16, v + 4);
+  } else if constexpr (N == 3) {
+    bload3(r, off, v);
+  } else if constexpr (N == 2) {
+    const u32x2 q = __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0);
+    const unsigned a = q.x, b = q.y;
+    v[0] = __builtin_bit_cast(float, a);
+    v[1] = __builtin_bit_cast(float, b);
+  } else if constexpr (N == 1) {
+    v[0] = bload1(r, off);
+  }
 }
 __device__ __forceinline__ void bstore1(__amdgpu_buffer_rsrc_t r, int off, float v) {
   __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, off, 0, 0);

@@ -180,6 +180,52 @@ static bool split_ok(int64_t chunks, int split, int64_t* cps) {
     return CT_S_INVALID;         \
   } while (0)
 
+// LDS layout of a direct schedule (k_direct.inc.h): the filter slice, then the
+// halo. Rows of the halo start at multiples of the width a thread's window is
+// read in (16 or 8 bytes), a channel group's filter words at an odd multiple
+// of theirs (the groups of a wave start in different banks), and both regions
+// take whole rows of the block's threads where they fit (chunks small enough
+// to be staged through registers always do). Where the padded tile exceeds the
+// LDS, the generic path runs with unpadded rows and slices, which the caller
+// has checked to fit. The ALT variant takes chunks of more words per thread
+// than its 128- or 256-register instances stage through registers (16, or 24
+// beside 16 or more accumulators), if their filter rows are whole 16-byte quads. Returns the bytes; sets g->spec, g->d_alt
+// and the pitches.
+static int64_t direct_lds_layout(const OpX& x, const ct_schedule& s, int64_t threads, Geom* g) {
+  using namespace direct_knob;
+  const ct_op& o = x.op;
+  const int mk = s.knob[MK], mw = s.knob[MW], ct = s.knob[CT], groups = s.knob[TK] / mk;
+  auto odd = [](int64_t words, int unit) {  // up to an odd multiple of unit
+    const int64_t u = cdiv(words, unit);
+    return (u % 2 ? u : u + 1) * unit;
+  };
+  for (;;) {
+    const bool padded = g->spec != SPEC_GENERIC;
+    const int step = mw * o.stride_w, xa = step % 4 == 0 ? 4 : (step % 2 == 0 ? 2 : 1);
+    const int64_t pitch = padded ? cdiv(g->iw_t, xa) * xa : g->iw_t;
+    const int64_t wpc = (int64_t)ct * o.r * o.s;  // filter words of an output channel
+    const int wa = mk > 1 || wpc % 4 == 0 ? 4 : 1;
+    const int64_t ks = padded ? odd(wpc * mk, wa) : wpc * mk;
+    const int64_t w0 = groups * ks, x0 = ct * g->ih_t * pitch;
+    int64_t wr = cdiv(w0, threads) * threads;
+    const int64_t xr = cdiv(x0, threads) * threads;
+    const bool alt = padded && wr + xr > (mk * mw >= 16 ? 24 : 16) * threads && wpc % 4 == 0 && x.kred % 4 == 0;
+    if (alt) wr = cdiv(w0, 4 * threads) * 4 * threads;  // whole rows of 16-byte quads
+    const bool rows = 4 * (cdiv(wr, 4) * 4 + xr) <= kMaxLdsBytes;
+    const int64_t wt = rows ? wr : w0, bytes = 4 * (cdiv(wt, 4) * 4 + (rows ? xr : x0));
+    if (padded && bytes > kMaxLdsBytes) {
+      g->spec = SPEC_GENERIC;
+      continue;
+    }
+    g->d_alt = alt && rows;
+    g->d_pitch = (int)pitch;
+    g->d_wpc = (int)wpc;
+    g->d_ks = (int)ks;
+    g->d_wt = (int)wt;
+    return bytes;
+  }
+}
+
 static int geom_direct(const OpX& x, const ct_schedule& s, Geom* g, std::string* why) {
   using namespace direct_knob;
   const FamilyDef& f = *family_def(CT_FAM_DIRECT_F32);
@@ -210,6 +256,13 @@ static int geom_direct(const OpX& x, const ct_schedule& s, Geom* g, std::string*
   int64_t lbytes = 0;
   if (lds) lbytes = 4 * ((int64_t)ctile * g->ih_t * g->iw_t + (int64_t)tk * ctile * o.r * o.s);
   if (lbytes > kMaxLdsBytes) REJECT("LDS tile too large");
+  if (g->spec == SPEC_GENERIC && o.dil_w == 1 && o.stride_w <= 2 && (o.s == 5 || o.s == 7))
+    g->spec = o.s == 5 ? (o.stride_w == 1 ? SPEC_ROW5_S1 : SPEC_ROW5_S2)
+                       : (o.stride_w == 1 ? SPEC_ROW7_S1 : SPEC_ROW7_S2);
+  if (lds)
+    lbytes = direct_lds_layout(x, s, threads, g);
+  else  // scalar filter loads where every wave lies inside one channel group
+    g->d_alt = g->spec != SPEC_GENERIC && toh * (tow / mw) % 64 == 0;
   g->tiles_h = cdiv(x.oh, toh);
   g->tiles_w = cdiv(x.ow, tow);
   g->tiles_k = cdiv(o.k, tk);
@@ -576,8 +629,10 @@ int ct_kernel_name(const ct_op* op, const ct_schedule* s, char* buf, int cap) {
   char tmp[128];
   switch (s->family) {
     case CT_FAM_DIRECT_F32:
-      std::snprintf(tmp, sizeof tmp, "direct_f32_kernel<%d, %d, %s, %d, %d>", k[direct_knob::MK],
-                    k[direct_knob::MW], tf(k[direct_knob::LDS]), (int)g.spec, k[direct_knob::UNR]);
+      std::snprintf(tmp, sizeof tmp, "direct_f32_kernel<%d, %d, %s, %d, %d, %s>", k[direct_knob::MK],
+                    k[direct_knob::MW], tf(k[direct_knob::LDS]), (int)g.spec,
+                    g.spec == SPEC_GENERIC ? k[direct_knob::UNR] : 1,
+                    tf(g.d_alt));
       break;
     case CT_FAM_DEPTHWISE_F32: {
       const int spec = g.spec == SPEC_3X3_S1 ? 3 : (g.spec == SPEC_3X3_S2 ? 4 : 0);

@@ -48,6 +48,63 @@ def test_depthwise_edges_match_oracle(op):
         check_close(op, yd.cpu().numpy(), ref, a, tag)
 
 
+def _f32(name, n, c, h, w, k, r, s, stride, pad):
+    return W.Op(name, n, c, h, w, k, r, s, stride, stride, pad[0], pad[1], 1, 1, 1, 0, 0)
+
+
+# direct family: channel counts below and off the ring's depth, windows wider than the
+# image, both strides of the 5- and 7-column paths with uneven padding and rectangular
+# filters, and shapes that stay on the generic path
+DIRECT_EDGES = [
+    _f32("c1", 2, 1, 5, 6, 9, 3, 3, 1, (1, 1)),
+    _f32("c13", 1, 13, 6, 3, 10, 3, 3, 2, (1, 1)),
+    _f32("pw_c7", 2, 7, 5, 9, 12, 1, 1, 1, (0, 0)),
+    _f32("pw_s2_c18", 1, 18, 9, 11, 20, 1, 1, 2, (0, 0)),
+    _f32("f5", 2, 3, 9, 13, 10, 5, 5, 1, (2, 2)),
+    _f32("f5s2", 1, 6, 11, 15, 18, 5, 5, 2, (2, 1)),
+    _f32("f7", 1, 4, 8, 5, 6, 7, 7, 1, (3, 3)),
+    _f32("f7s2", 1, 3, 21, 18, 20, 7, 7, 2, (3, 3)),
+    _f32("rect2x5", 1, 9, 7, 12, 8, 2, 5, 1, (1, 0)),
+    _f32("rect3x7s2", 2, 5, 9, 16, 8, 3, 7, 2, (0, 4)),
+    _f32("f4", 1, 5, 9, 10, 8, 4, 4, 1, (1, 1)),
+    W.Op("dilh5", 1, 4, 14, 10, 8, 3, 5, 1, 1, 2, 2, 2, 1, 1, 0, 0),
+]
+
+
+@pytest.mark.parametrize("op", DIRECT_EDGES, ids=lambda o: o.name)
+def test_direct_edges_match_oracle(op):
+    x, w = make_inputs(op, "uniform", seed=43)
+    ref, a = reference(op, x, w)
+    xd, wd, yd = to_device(op, x, w)
+    space = [s for s in L.ct_valid_space(op) if s.family == W.FAM_DIRECT_F32]
+    # one schedule of every (mk, mw, lds), then a sample
+    by = {}
+    for s in random.Random(8).sample(space, len(space)):
+        by.setdefault((s.knob[3], s.knob[4], s.knob[5]), s)
+    for s in list(by.values()) + random.Random(9).sample(space, min(40, len(space))):
+        tag = "%s %s" % (op.name, sched_str(s))
+        note(tag)
+        yd.fill_(float("nan"))
+        L.conv2d_run(op, s, xd, wd, yd)
+        check_close(op, yd.cpu().numpy(), ref, a, tag, split=4)
+
+
+def test_direct_tiles_whose_padded_layout_exceeds_the_lds_run_generic():
+    op = W.conv("b3x3s2", 1, 64, 30, 64, 3, 2)
+    x, w = make_inputs(op, "uniform", seed=44)
+    ref, a = reference(op, x, w)
+    xd, wd, yd = to_device(op, x, w)
+    for knobs in ((14, 16, 32, 2, 4, 1, 32, 1, 1), (14, 16, 32, 2, 4, 1, 32, 2, 2), (14, 16, 32, 2, 4, 1, 16, 1, 1)):
+        s = L.make_schedule(W.FAM_DIRECT_F32, knobs)
+        assert L.ct_validate(op, s) == L.S_OK
+        generic = ", 0, " in L.ct_kernel_name(op, s)
+        assert generic == (knobs[6] == 32)
+        note("b3x3s2 " + sched_str(s))
+        yd.fill_(float("nan"))
+        L.conv2d_run(op, s, xd, wd, yd)
+        check_close(op, yd.cpu().numpy(), ref, a, sched_str(s), split=4)
+
+
 def test_depthwise_planes_beyond_the_32_bit_part_offsets():
     # two planes of 512 MB + : a block's planes span more than 2^30 bytes
     op = _dw("huge", 1, 2, 8200, 16400, 3, 3, 1, (1, 1))
