@@ -17,6 +17,12 @@ namespace ct {
 constexpr int kMaxLdsBytes = 160 * 1024;  // per-block LDS budget (the gfx950 workgroup maximum)
 constexpr int kMaxThreads = 1024;
 constexpr int kMinThreads = 32;
+// LDS that several bf16 chunks copied together may take: four such blocks share a CU
+// (64 KB: 1.01 times as fast on the whole GPU, 0.97 times on a quarter)
+constexpr int kBf16GroupBytes = 40 << 10;
+// bf16 without LDS: most k-steps of fragments in flight beside `frags` of them each (4
+// steps of 5 and more fragments, 80 to 128 registers: 0.99 times as fast as 2)
+constexpr int bf16_most_steps(int frags) { return frags <= 2 ? 8 : frags <= 4 ? 4 : 2; }
 constexpr int kMaxLoadsPerThread = 8;     // register staging bound of the GEMM loaders
 // fp32 MFMA family, stages 3 (four loader waves): the largest accumulator
 // tile in registers that still leaves room, two waves per SIMD, for the copy
@@ -93,6 +99,8 @@ struct Geom {
   int bm, bn;         // GEMM block tile (rows x cols)
   int chunks;         // reduction chunks in total
   int chunks_per_split;
+  int bf_group;         // bf16: chunks staged in LDS at once
+  int bf_ring;          // bf16 without LDS: k-steps of fragments in flight
   int a_loads, b_loads;  // per-thread staged loads per chunk (GEMM families)
   int kc, kcp;           // reduction rows per chunk, and padded to whole k-steps
   int cpcp, lda, tph, tpw;  // fp32 MFMA family: padded channels per chunk, filter row pitch, pixel rectangle

@@ -7,18 +7,38 @@
 // the reduction, so every MFMA fragment is one 16-byte load of 8 bf16.
 //
 // A block owns a BM x BN tile (BM = WM*TM*MF pixels, BN = WN*TN*MF
-// channels), one wave per WM x WN sub-tile. LDS = 0 loads each wave's
-// fragments straight from global memory, a whole reduction chunk (KC) at a
-// time, the next chunk's loads in flight during the current chunk's MFMAs
-// (two register sets, for TM + TN <= 4); LDS = 1 stages the chunk's A and B tiles
-// in LDS with coalesced 16-byte loads shared by the block. SPLIT > 1 spreads
+// channels), one wave per WM x WN sub-tile. SPLIT > 1 spreads
 // contiguous chunk ranges over grid.y (partials added in split order by a
 // second kernel). SWZ = 1 renumbers blocks so that the tiles each XCD
 // receives (blocks are dealt to the 8 XCDs in turn) are contiguous, which
 // keeps a row band of x in one XCD's L2.
-// All global loads are bounds-checked (C is a multiple of 8, so a 16-byte
-// group is either wholly inside the tensor or wholly outside).
+//
+// What bounds it: a tile has few reduction steps (C = 16 to 960 is 1 to 30 of
+// 32), so the loads' latency, once per step or chunk, and the instructions
+// beside the loads and matrix products.
+//   * LDS = 0 loads each wave's fragments straight from global memory through
+//     a ring of D k-steps, each reloaded right after its products. D is the
+//     smallest of 1, 2, 4, 8 that holds the wave's whole reduction: a longer
+//     one loads steps that are not there and takes registers from other waves
+//     (0.78 times as fast at one step on a quarter), up to
+//     bf16_most_steps().
+//   * LDS = 1 copies chunks of KC straight into LDS, 16 bytes per lane, as
+//     many chunks as fit kBf16GroupBytes before the first wait, so that most
+//     tiles wait once. Rows lie unpadded; the 16-byte groups of a row are
+//     permuted by the low bits of its number, so that the 16 rows a fragment
+//     reads at one k lie in distinct banks.
+//   * Reads are range-checked buffer loads from a base that advances with k:
+//     no bounds branch, no select, no address arithmetic per load.
+// Measured, 3076 sampled schedules of the MobileNet-v2 b16 pointwise layers and
+// a ragged one, summed, against one chunk through registers (LDS = 1) and two
+// chunks of fragments with clamped addresses (LDS = 0): 39.3 to 30.0 ms on the
+// whole GPU, 69.3 to 47.6 ms on a quarter (LDS = 1: 23.1 to 16.0 and 41.4 to
+// 24.6; LDS = 0: 16.2 to 14.0 and 27.9 to 23.0). Channels as the matrix
+// instruction's rows, for 16-byte stores, lost: 30 % slower at K = 96 and up,
+// where a store then touches 16 pixels instead of 4.
 #include <hip/hip_runtime.h>
+
+#include <type_traits>
 
 #include "ct_internal.h"
 #include "k_util.h"
@@ -26,13 +46,14 @@
 namespace ct {
 
 struct IgBf16Args {
-  int N, H, W, C, K, OH, OW, sh, sw;
+  int H, W, C, K, sh, sw;
   int npix;
-  int wm, wn, kc;
+  uint32_t xbytes, wbytes;
+  int wn_shift, kc;
   int bm, bn, threads;
-  int cps, chunks;
-  int a_loads, b_loads;
+  int cps, chunks, group;  // chunks in LDS at once
   int tiles_m, tiles_n, swz;
+  FastDiv dtn, dohw, dow;
   int64_t ny;
 };
 
@@ -56,26 +77,20 @@ struct MfmaBf16<32> {
 };
 
 __host__ __device__ constexpr int bf16_max_threads(int acc_regs) { return acc_regs <= 64 ? 512 : 256; }
-constexpr int kBf16MaxSteps = 4;  // k-steps of fragments held in registers (LDS = 0)
+// Byte offset past every operand (fewer than 2^32 - 15 bytes): reads as 0.
+constexpr unsigned kOobBytes = 0xFFFFFFF0u;
 
-__device__ inline int pixel_offset(int m, const IgBf16Args& a) {
-  if (a.sh == 1 && a.sw == 1) return m * a.C;  // OH = H, OW = W
-  const int ohw = a.OH * a.OW;
-  const int n = m / ohw;
-  const int rem = m - n * ohw;
-  const int oh = rem / a.OW, ow = rem - oh * a.OW;
+// Element offset of output pixel m's channels in x.
+__device__ __forceinline__ int pixel_offset(int m, const IgBf16Args& a) {
+  const int n = fdiv(m, a.dohw), rem = m - n * a.dohw.d;
+  const int oh = fdiv(rem, a.dow), ow = rem - oh * a.dow.d;
   return ((n * a.H + oh * a.sh) * a.W + ow * a.sw) * a.C;
 }
-
-// 16-byte fragment load, branch-free: an invalid fragment reads the tensor's
-// first 16 bytes and is replaced by zeros.
-__device__ inline bf16x8 load8(const unsigned short* base, int64_t off, bool ok) {
-  const u32x4 v = *(const u32x4*)(base + (ok ? off : 0));
-  const u32x4 z = {0u, 0u, 0u, 0u};
-  return __builtin_bit_cast(bf16x8, ok ? v : z);
+__device__ __forceinline__ bf16x8 load8(__amdgpu_buffer_rsrc_t r, unsigned off) {
+  return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0));
 }
 
-template <int MF, int TM, int TN, bool LDS>
+template <int MF, int TM, int TN, int KC, int D>
 __global__ void __launch_bounds__(bf16_max_threads(TM * TN * MfmaBf16<MF>::ACC))
 igemm_bf16_kernel(const unsigned short* __restrict__ x, const unsigned short* __restrict__ w,
                   float* __restrict__ out, IgBf16Args a) {
@@ -87,17 +102,16 @@ igemm_bf16_kernel(const unsigned short* __restrict__ x, const unsigned short* __
   const int T = a.tiles_m * a.tiles_n;
   int b = blockIdx.x;
   if (a.swz) b = xcd_band_tile(b, T);
-  const int tmi = b / a.tiles_n, tni = b - tmi * a.tiles_n;
+  const int tmi = fdiv(b, a.dtn), tni = b - tmi * a.tiles_n;
   const int m0 = tmi * a.bm, n0 = tni * a.bn, sp = blockIdx.y;
 
   const int t = threadIdx.x, lane = t & 63, wave = wave_id();
-  const int wmi = wave / a.wn, wni = wave - wmi * a.wn;
+  const int wmi = wave >> a.wn_shift, wni = wave - (wmi << a.wn_shift);
   const int m_off = wmi * TM * MF, n_off = wni * TN * MF;
-  const int lrow = lane % MF, kq = (lane / MF) * 8;  // fragment row and k offset of this lane
+  const int lrow = lane % MF, kg = lane / MF;  // fragment row and 8-value group of this lane
 
   const int ch_begin = sp * a.cps;
   const int ch_end = min(a.chunks, ch_begin + a.cps);
-  const int kr_end = min(a.C, ch_end * a.kc);
 
   V acc[TM][TN];
 #pragma unroll
@@ -107,132 +121,143 @@ igemm_bf16_kernel(const unsigned short* __restrict__ x, const unsigned short* __
 #pragma unroll
       for (int e = 0; e < ACC; ++e) acc[i][j][e] = 0.f;
 
-  if constexpr (!LDS) {
-    int aoff[TM], boff[TN];
-    bool aok[TM], bok[TN];
+  if constexpr (KC == 0) {
+    unsigned aoff[TM], boff[TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
       const int m = m0 + m_off + i * MF + lrow;
-      aok[i] = m < a.npix;
-      aoff[i] = aok[i] ? pixel_offset(m, a) : 0;
+      aoff[i] = m < a.npix ? 2u * (unsigned)pixel_offset(m, a) + 16u * kg : kOobBytes;
     }
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
       const int n = n0 + n_off + j * MF + lrow;
-      bok[j] = n < a.K;
-      boff[j] = bok[j] ? n * a.C : 0;
+      boff[j] = n < a.K ? 2u * (unsigned)(n * a.C) + 16u * kg : kOobBytes;
     }
-    const int steps = a.kc / KSTEP;
-    // The fragments of chunk ch+1 are loaded into a second register set
-    // while the MFMAs of chunk ch run (two sets, used alternately).
-    using FragA = bf16x8[kBf16MaxSteps][TM];
-    using FragB = bf16x8[kBf16MaxSteps][TN];
-    auto load_chunk = [&](int ch, FragA& fa, FragB& fb) {
-      const int kr0 = ch * a.kc;
+    bf16x8 fa[D][TM], fb[D][TN];
+    const int kb = ch_begin * a.kc, n = (min(a.C, ch_end * a.kc) - kb + KSTEP - 1) / KSTEP;
+    auto load = [&](int u, int st) __attribute__((always_inline)) {
+      const bool live = st < n;  // steps past the end read 0 and are not used
+      const int k = live ? kb + st * KSTEP : 0;
+      if (live && k + KSTEP > a.C) {  // the reduction's last step: what follows reads 0
+        const bool ok = k + 8 * kg < a.C;
 #pragma unroll
-      for (int st = 0; st < kBf16MaxSteps; ++st) {
-        const int k = kr0 + st * KSTEP + kq;
-        const bool kok = st < steps && k < kr_end;
+        for (int i = 0; i < TM; ++i) aoff[i] = ok ? aoff[i] : kOobBytes;
 #pragma unroll
-        for (int i = 0; i < TM; ++i) fa[st][i] = load8(x, (int64_t)aoff[i] + k, kok && aok[i]);
-#pragma unroll
-        for (int j = 0; j < TN; ++j) fb[st][j] = load8(w, (int64_t)boff[j] + k, kok && bok[j]);
+        for (int j = 0; j < TN; ++j) boff[j] = ok ? boff[j] : kOobBytes;
       }
+      const __amdgpu_buffer_rsrc_t rx = make_rsrc(x + k, live ? (int64_t)(a.xbytes - 2u * (uint32_t)k) : 0);
+      const __amdgpu_buffer_rsrc_t rw = make_rsrc(w + k, live ? (int64_t)(a.wbytes - 2u * (uint32_t)k) : 0);
+#pragma unroll
+      for (int i = 0; i < TM; ++i) fa[u][i] = load8(rx, aoff[i]);
+#pragma unroll
+      for (int j = 0; j < TN; ++j) fb[u][j] = load8(rw, boff[j]);
+      __builtin_amdgcn_sched_barrier(0);
     };
-    auto mma_chunk = [&](const FragA& fa, const FragB& fb) {
+    auto mma = [&](int u) __attribute__((always_inline)) {
 #pragma unroll
-      for (int st = 0; st < kBf16MaxSteps; ++st) {
-        if (st < steps) {
+      for (int i = 0; i < TM; ++i)
 #pragma unroll
-          for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j) acc[i][j] = M::op(fa[st][i], fb[st][j], acc[i][j]);
-        }
-      }
+        for (int j = 0; j < TN; ++j) acc[i][j] = M::op(fa[u][i], fb[u][j], acc[i][j]);
+      __builtin_amdgcn_sched_barrier(0);
     };
-    if constexpr (TM + TN <= 4) {
-      FragA fa0, fa1;
-      FragB fb0, fb1;
-      if (ch_begin < ch_end) load_chunk(ch_begin, fa0, fb0);
-      for (int ch = ch_begin; ch < ch_end; ch += 2) {
-        if (ch + 1 < ch_end) load_chunk(ch + 1, fa1, fb1);
-        mma_chunk(fa0, fb0);
-        if (ch + 1 >= ch_end) break;
-        if (ch + 2 < ch_end) load_chunk(ch + 2, fa0, fb0);
-        mma_chunk(fa1, fb1);
+#pragma unroll
+    for (int u = 0; u < D; ++u) load(u, u);
+    int st = 0;
+    for (; st + D < n; st += D)
+#pragma unroll
+      for (int u = 0; u < D; ++u) {
+        mma(u);
+        load(u, st + D + u);
       }
-    } else {
-      // larger fragment sets: one set (two would spill registers)
-      FragA fa0;
-      FragB fb0;
-      for (int ch = ch_begin; ch < ch_end; ++ch) {
-        load_chunk(ch, fa0, fb0);
-        mma_chunk(fa0, fb0);
-      }
-    }
+#pragma unroll
+    for (int u = 0; u < D; ++u)
+      if (st + u < n) mma(u);
   } else {
     extern __shared__ unsigned short lds16[];
-    const int pitch = a.kc + 8;  // bf16 elements per LDS row (16-byte pad)
-    unsigned short* As = lds16;
-    unsigned short* Bs = lds16 + a.bm * pitch;
-    const int vpr = a.kc / 8;  // 16-byte vectors per row
-    const int vcol = t % vpr, row0 = t / vpr, rstep = a.threads / vpr;
-    int aoff[kMaxLoadsPerThread];
-    bool aok[kMaxLoadsPerThread];
+    constexpr int VPR = KC / 8, RPC = 64 / VPR;  // 16-byte groups of a row, rows of a wave's copy
+    constexpr int SW = VPR == 4 ? 2 : VPR == 8 ? 1 : 0;
+    const int nw_shift = 31 - __builtin_clz(a.threads >> 6), qa = a.bm / RPC, q_end = (a.bm + a.bn) / RPC;
+    // this wave's copies q = wave + i * waves: the first na of its nq are rows of x
+    const int nq = (q_end - wave + (1 << nw_shift) - 1) >> nw_shift;
+    const int na = max(0, (qa - wave + (1 << nw_shift) - 1) >> nw_shift);
+    // group of this lane in copy q: rows 16 apart differ in the same way
+    auto col = [&](int q) __attribute__((always_inline)) {
+      return (lane % VPR) ^ (((q * RPC + lane / VPR) >> SW) & (VPR - 1));
+    };
+    unsigned off[2 * kMaxLoadsPerThread];
 #pragma unroll
-    for (int i = 0; i < kMaxLoadsPerThread; ++i) {
-      const int m = m0 + row0 + i * rstep;
-      aok[i] = i < a.a_loads && row0 + i * rstep < a.bm && m < a.npix;
-      aoff[i] = aok[i] ? pixel_offset(m, a) : 0;
+    for (int i = 0; i < 2 * kMaxLoadsPerThread; ++i) {
+      const int q = wave + (i << nw_shift);
+      if (i < nq) {
+        const int r = q * RPC + lane / VPR, m = m0 + r, n = n0 + r - a.bm;
+        if (i < na)
+          off[i] = m < a.npix ? 2u * (unsigned)pixel_offset(m, a) + 16u * col(q) : kOobBytes;
+        else
+          off[i] = n < a.K ? 2u * (unsigned)(n * a.C) + 16u * col(q) : kOobBytes;
+      }
     }
-    for (int ch = ch_begin; ch < ch_end; ++ch) {
-      const int k = ch * a.kc + vcol * 8;
-      const bool kok = k < kr_end;
-      // loads are issued unconditionally (invalid ones read offset 0) and the
-      // zero-select happens at the LDS store, so all loads are in flight at once
-      u32x4 ra[kMaxLoadsPerThread], rb[kMaxLoadsPerThread];
-      unsigned oka = 0, okb = 0;
+    auto copy_chunk = [&](int ch, unsigned short* dst) __attribute__((always_inline)) {
+      const int k = ch * KC;
+      const __amdgpu_buffer_rsrc_t rx = make_rsrc(x + k, (int64_t)(a.xbytes - 2u * (uint32_t)k));
+      const __amdgpu_buffer_rsrc_t rw = make_rsrc(w + k, (int64_t)(a.wbytes - 2u * (uint32_t)k));
+      // opaque here, so that the comparisons are made where they are used
+      // rather than kept in scalar register pairs, which do not suffice
+      int cq = nq, ca = na;
+      asm volatile("" : "+s"(cq), "+s"(ca));
+      auto copies = [&](auto tail) __attribute__((always_inline)) {
 #pragma unroll
-      for (int i = 0; i < kMaxLoadsPerThread; ++i) {
-        if (i < a.a_loads) {
-          const bool ok = kok && aok[i];
-          ra[i] = *(const u32x4*)(x + (ok ? (int64_t)aoff[i] + k : 0));
-          oka |= (unsigned)ok << i;
-        }
-      }
+        for (int i0 = 0; i0 < 2 * kMaxLoadsPerThread; i0 += 4)
+          if (i0 < cq) {
 #pragma unroll
-      for (int i = 0; i < kMaxLoadsPerThread; ++i) {
-        if (i < a.b_loads) {
-          const int rr = row0 + i * rstep;
-          const int n = n0 + rr;
-          const bool ok = rr < a.bn && n < a.K && kok;
-          rb[i] = *(const u32x4*)(w + (ok ? (int64_t)n * a.C + k : 0));
-          okb |= (unsigned)ok << i;
-        }
-      }
+            for (int i = i0; i < i0 + 4; ++i)
+              if (i < cq) {
+                const int q = wave + (i << nw_shift);
+                unsigned o = off[i];
+                if constexpr (tail.value) o = k + 8 * col(q) < a.C ? o : kOobBytes;
+                copy16_to_lds(i < ca ? rx : rw, (float*)(dst + q * 512), (int)o);
+              }
+          }
+      };
+      if (k + KC <= a.C)
+        copies(std::false_type{});
+      else
+        copies(std::true_type{});
+    };
+    const int csw = (lrow >> SW) & (VPR - 1);
+    auto mma_step = [&](const unsigned short* src, int st) __attribute__((always_inline)) {
+      const int c = (st * (KSTEP / 8) + kg) ^ csw;
+      bf16x8 fa[TM], fb[TN];
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+        fa[i] = __builtin_bit_cast(bf16x8, *(const u32x4*)(src + (m_off + i * MF + lrow) * KC + c * 8));
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+        fb[j] = __builtin_bit_cast(bf16x8, *(const u32x4*)(src + (a.bm + n_off + j * MF + lrow) * KC + c * 8));
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = M::op(fa[i], fb[j], acc[i][j]);
+    };
+    const int stage = (a.bm + a.bn) * KC;
+    for (int c0 = ch_begin; c0 < ch_end; c0 += a.group) {
+      const int nc = min(a.group, ch_end - c0);
+      if (c0 > ch_begin) __syncthreads();
+      for (int c = 0; c < nc; ++c) copy_chunk(c0 + c, lds16 + c * stage);
+      wait_copies();
       __syncthreads();
-      const u32x4 z = {0u, 0u, 0u, 0u};
+      for (int c = 0; c < nc; ++c) {
+        const int left = a.C - (c0 + c) * KC;
+        const unsigned short* src = lds16 + c * stage;
+        mma_step(src, 0);
 #pragma unroll
-      for (int i = 0; i < kMaxLoadsPerThread; ++i) {
-        const int rr = row0 + i * rstep;
-        if (i < a.a_loads && rr < a.bm) *(u32x4*)(As + rr * pitch + vcol * 8) = (oka >> i & 1u) ? ra[i] : z;
-        if (i < a.b_loads && rr < a.bn) *(u32x4*)(Bs + rr * pitch + vcol * 8) = (okb >> i & 1u) ? rb[i] : z;
-      }
-      __syncthreads();
-      const int steps = a.kc / KSTEP;
-      for (int st = 0; st < steps; ++st) {
-        const int kk = st * KSTEP + kq;
-        bf16x8 fa[TM], fb[TN];
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-          fa[i] = __builtin_bit_cast(bf16x8, *(const u32x4*)(As + (m_off + i * MF + lrow) * pitch + kk));
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-          fb[j] = __builtin_bit_cast(bf16x8, *(const u32x4*)(Bs + (n_off + j * MF + lrow) * pitch + kk));
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-          for (int j = 0; j < TN; ++j) acc[i][j] = M::op(fa[i], fb[j], acc[i][j]);
+        for (int st = 1; st < KC / KSTEP; ++st)
+          if (st * KSTEP < left) mma_step(src, st);
+        // A copy of the accumulators at this loop's end has come without the
+        // wait that a matrix result needs (two of the first four of a lane
+        // were stale): wait here, 18 cycles a chunk.
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("s_nop 15\n\ts_nop 1" :::);
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
   }
@@ -280,26 +305,36 @@ igemm_bf16_kernel(const unsigned short* __restrict__ x, const unsigned short* __
 using IgBf16Fn = void (*)(const unsigned short*, const unsigned short*, float*, IgBf16Args);
 
 template <int MF, int TM, int TN>
-static IgBf16Fn bf_pick_lds(int lds) {
-  if constexpr (TM * TN * MfmaBf16<MF>::ACC > 128)
+static IgBf16Fn bf_pick_kc(int kc, int ring) {
+  if constexpr (TM * TN * MfmaBf16<MF>::ACC > 128) {
     return nullptr;  // accumulator tiles the validator rejects: not instantiated
-  else
-    return lds ? igemm_bf16_kernel<MF, TM, TN, true> : igemm_bf16_kernel<MF, TM, TN, false>;
+  } else {
+    switch (kc) {
+      case 32: return igemm_bf16_kernel<MF, TM, TN, 32, 0>;
+      case 64: return igemm_bf16_kernel<MF, TM, TN, 64, 0>;
+      case 128: return igemm_bf16_kernel<MF, TM, TN, 128, 0>;
+    }
+    constexpr int most = bf16_most_steps(TM + TN);
+    if (ring == 1) return igemm_bf16_kernel<MF, TM, TN, 0, 1>;
+    if (ring == 2) return igemm_bf16_kernel<MF, TM, TN, 0, 2>;
+    if (ring == 4) return igemm_bf16_kernel<MF, TM, TN, 0, most < 4 ? most : 4>;
+    return igemm_bf16_kernel<MF, TM, TN, 0, most>;
+  }
 }
 template <int MF, int TM>
-static IgBf16Fn bf_pick_tn(int tn, int lds) {
+static IgBf16Fn bf_pick_tn(int tn, int kc, int ring) {
   switch (tn) {
-    case 1: return bf_pick_lds<MF, TM, 1>(lds);
-    case 2: return bf_pick_lds<MF, TM, 2>(lds);
-    default: return bf_pick_lds<MF, TM, 4>(lds);
+    case 1: return bf_pick_kc<MF, TM, 1>(kc, ring);
+    case 2: return bf_pick_kc<MF, TM, 2>(kc, ring);
+    default: return bf_pick_kc<MF, TM, 4>(kc, ring);
   }
 }
 template <int MF>
-static IgBf16Fn bf_pick_tm(int tm, int tn, int lds) {
+static IgBf16Fn bf_pick_tm(int tm, int tn, int kc, int ring) {
   switch (tm) {
-    case 1: return bf_pick_tn<MF, 1>(tn, lds);
-    case 2: return bf_pick_tn<MF, 2>(tn, lds);
-    default: return bf_pick_tn<MF, 4>(tn, lds);
+    case 1: return bf_pick_tn<MF, 1>(tn, kc, ring);
+    case 2: return bf_pick_tn<MF, 2>(tn, kc, ring);
+    default: return bf_pick_tn<MF, 4>(tn, kc, ring);
   }
 }
 
@@ -308,17 +343,20 @@ int launch_igemm_bf16(const OpX& x, const ct_schedule& s, const Geom& g, const v
   using namespace bf16_knob;
   const ct_op& o = x.op;
   IgBf16Args a;
-  a.N = o.n; a.H = o.h; a.W = o.w; a.C = o.c; a.K = o.k; a.OH = (int)x.oh; a.OW = (int)x.ow;
+  a.H = o.h; a.W = o.w; a.C = o.c; a.K = o.k;
   a.sh = o.stride_h; a.sw = o.stride_w;
   a.npix = (int)x.npix;
-  a.wm = s.knob[WM]; a.wn = s.knob[WN]; a.kc = s.knob[KC];
+  a.xbytes = (uint32_t)(2 * x.nx); a.wbytes = (uint32_t)(2 * x.nw);
+  a.wn_shift = s.knob[WN] == 4 ? 2 : s.knob[WN] == 2 ? 1 : 0; a.kc = s.knob[KC];
   a.bm = g.bm; a.bn = g.bn; a.threads = g.threads;
   a.cps = g.chunks_per_split; a.chunks = g.chunks;
-  a.a_loads = g.a_loads; a.b_loads = g.b_loads;
+  a.group = g.bf_group;
+  a.dtn = make_fastdiv(g.tiles_k); a.dohw = make_fastdiv(x.oh * x.ow); a.dow = make_fastdiv(x.ow);
   a.tiles_m = (int)g.tiles_h; a.tiles_n = (int)g.tiles_k; a.swz = s.knob[SWZ];
   a.ny = x.ny;
-  IgBf16Fn fn = s.knob[MF] == 32 ? bf_pick_tm<32>(s.knob[TM], s.knob[TN], s.knob[LDS])
-                                 : bf_pick_tm<16>(s.knob[TM], s.knob[TN], s.knob[LDS]);
+  const int kc = s.knob[LDS] ? s.knob[KC] : 0;
+  IgBf16Fn fn = s.knob[MF] == 32 ? bf_pick_tm<32>(s.knob[TM], s.knob[TN], kc, g.bf_ring)
+                                 : bf_pick_tm<16>(s.knob[TM], s.knob[TN], kc, g.bf_ring);
   if (!fn) {
     set_error("igemm_bf16: no kernel instance for this accumulator tile");
     return -2;

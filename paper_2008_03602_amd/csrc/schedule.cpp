@@ -351,6 +351,19 @@ static int geom_igemm_bf16(const OpX& x, const ct_schedule& s, Geom* g, std::str
     g->a_loads = g->b_loads = 0;
   }
   if (lbytes > kMaxLdsBytes) REJECT("LDS tile too large");
+  g->bf_group = 1;
+  g->bf_ring = 0;
+  if (!lds) {
+    const int64_t steps = cdiv(std::min<int64_t>(o.c, cps * kc), mf == 32 ? 16 : 32);
+    const int most = bf16_most_steps(tm + tn);
+    g->bf_ring = 1;
+    while (g->bf_ring < steps && g->bf_ring < most) g->bf_ring *= 2;
+  }
+  if (lds) {  // rows lie unpadded in LDS, swizzled, several chunks at once
+    const int64_t chunk = 2 * (int64_t)(bm + bn) * kc;
+    g->bf_group = (int)std::max<int64_t>(1, std::min<int64_t>(cps, kBf16GroupBytes / chunk));
+    lbytes = g->bf_group * chunk;
+  }
   g->bm = bm;
   g->bn = bn;
   g->tiles_h = cdiv(x.npix, bm);  // row tiles
@@ -644,8 +657,8 @@ int ct_kernel_name(const ct_op* op, const ct_schedule* s, char* buf, int cap) {
       break;
     }
     case CT_FAM_IGEMM_BF16:
-      std::snprintf(tmp, sizeof tmp, "igemm_bf16_kernel<%d, %d, %d, %s>", k[bf16_knob::MF], k[bf16_knob::TM],
-                    k[bf16_knob::TN], tf(k[bf16_knob::LDS]));
+      std::snprintf(tmp, sizeof tmp, "igemm_bf16_kernel<%d, %d, %d, %d, %d>", k[bf16_knob::MF], k[bf16_knob::TM],
+                    k[bf16_knob::TN], k[bf16_knob::LDS] ? k[bf16_knob::KC] : 0, g.bf_ring);
       break;
     default:
       std::snprintf(tmp, sizeof tmp, "igemm_f32_kernel<%d, %d, %d, %d, %d>", k[f32g_knob::MF], k[f32g_knob::TM],

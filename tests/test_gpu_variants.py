@@ -128,3 +128,61 @@ def test_depthwise_planes_beyond_the_32_bit_part_offsets():
         L.conv2d_run(op, s, xd, wd, yd)
         # 9 products of at most 1: both sums err by at most 9 roundings of at most 9 * 2^-24
         assert float((yd - ref).abs().max()) <= 2 * 9 * 9 * 2.0 ** -24
+
+
+def _pw(name, n, c, h, w, k, stride=1):
+    return W.Op(name, n, c, h, w, k, 1, 1, stride, stride, 0, 0, 1, 1, 1, W.DT_BF16, W.LAYOUT_NHWC)
+
+
+# reductions of one group of 8, off every chunk and step length, and longer than the steps
+# in flight; channel and pixel counts off every tile; a stride
+BF16_EDGES = [
+    _pw("c8k1", 1, 8, 5, 7, 1),
+    _pw("c24k17", 3, 24, 5, 5, 17),
+    _pw("c40k30", 2, 40, 9, 7, 30),
+    _pw("c136k65s2", 2, 136, 9, 11, 65, 2),
+    _pw("c328k130", 1, 328, 11, 13, 130),
+    _pw("c648k48", 1, 648, 7, 9, 48),
+]
+
+
+@pytest.mark.parametrize("op", BF16_EDGES, ids=lambda o: o.name)
+def test_bf16_edges_match_oracle(op):
+    x, w = make_inputs(op, "uniform", seed=45)
+    ref, a = reference(op, x, w)
+    xd, wd, yd = to_device(op, x, w)
+    space = L.ct_valid_space(op)
+    # one schedule of every kernel, then a sample
+    by = {}
+    for s in random.Random(10).sample(space, len(space)):
+        by.setdefault(L.ct_kernel_name(op, s), s)
+    for s in list(by.values()) + random.Random(11).sample(space, min(40, len(space))):
+        tag = "%s %s" % (op.name, sched_str(s))
+        note(tag)
+        yd.fill_(float("nan"))
+        L.conv2d_run(op, s, xd, wd, yd)
+        check_close(op, yd.cpu().numpy(), ref, a, tag, split=4)
+
+
+def test_bf16_operand_beyond_2_gib():
+    # x of 3.3 GB: byte offsets past 2^31, and the last pixels' reads end near the buffer's
+    op = _pw("huge", 1, 960, 1280, 1343, 16)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(8)
+    xd = torch.empty(op.x_shape(), dtype=torch.bfloat16, device="cuda")
+    for r in range(0, op.h, 128):
+        xd[:, r:r + 128] = torch.rand(xd[:, r:r + 128].shape, generator=gen, device="cuda") * 2 - 1
+    wd = (torch.rand(op.w_shape(), generator=gen, device="cuda") * 2 - 1).to(torch.bfloat16)
+    yd = torch.empty(op.y_shape(), device="cuda")
+    wt = wd.reshape(op.k, op.c).double().t().contiguous()
+    for lds in (0, 1):
+        s = L.make_schedule(W.FAM_IGEMM_BF16, (16, 2, 1, 2, 1, 128 if lds else 32, lds, 1, 0))
+        assert L.ct_validate(op, s) == L.S_OK
+        note("huge " + sched_str(s))
+        yd.fill_(float("nan"))
+        torch.cuda.synchronize()
+        L.conv2d_run(op, s, xd, wd, yd)
+        for r in (0, 640, 1216):  # the start, the 2 GiB boundary and past it
+            d = yd[0, r:r + 64].reshape(-1, op.k).double() - xd[0, r:r + 64].reshape(-1, op.c).double() @ wt
+            # 960 exact products of at most 1, and as many roundings
+            assert float(d.abs().max()) <= 962 * 960 * 2.0 ** -24
