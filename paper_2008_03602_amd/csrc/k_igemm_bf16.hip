@@ -354,16 +354,20 @@ int launch_igemm_bf16(const OpX& x, const ct_schedule& s, const Geom& g, const v
   a.dtn = make_fastdiv(g.tiles_k); a.dohw = make_fastdiv(x.oh * x.ow); a.dow = make_fastdiv(x.ow);
   a.tiles_m = (int)g.tiles_h; a.tiles_n = (int)g.tiles_k; a.swz = s.knob[SWZ];
   a.ny = x.ny;
-  const int kc = s.knob[LDS] ? s.knob[KC] : 0;
-  IgBf16Fn fn = s.knob[MF] == 32 ? bf_pick_tm<32>(s.knob[TM], s.knob[TN], kc, g.bf_ring)
-                                 : bf_pick_tm<16>(s.knob[TM], s.knob[TN], kc, g.bf_ring);
+  // copies into LDS take 16 bytes at 16-byte addresses; tensors off them are
+  // read without LDS, in the same order
+  const bool aligned = ((uintptr_t)xin | (uintptr_t)w) % 16 == 0;
+  const int kc = s.knob[LDS] && aligned ? s.knob[KC] : 0;
+  const int ring = s.knob[LDS] ? bf16_most_steps(s.knob[TM] + s.knob[TN]) : g.bf_ring;
+  IgBf16Fn fn = s.knob[MF] == 32 ? bf_pick_tm<32>(s.knob[TM], s.knob[TN], kc, ring)
+                                 : bf_pick_tm<16>(s.knob[TM], s.knob[TN], kc, ring);
   if (!fn) {
     set_error("igemm_bf16: no kernel instance for this accumulator tile");
     return -2;
   }
   dim3 grid((unsigned)(g.tiles_h * g.tiles_k), (unsigned)g.split);
   float* out = g.split > 1 ? ws : (float*)y;
-  hipLaunchKernelGGL(fn, grid, dim3(g.threads), g.lds_bytes, (hipStream_t)stream,
+  hipLaunchKernelGGL(fn, grid, dim3(g.threads), kc ? g.lds_bytes : 0, (hipStream_t)stream,
                      (const unsigned short*)xin, (const unsigned short*)w, out, a);
   if (hipGetLastError() != hipSuccess) return -1;
   if (g.split > 1) return launch_split_reduce(ws, (float*)y, x.ny, g.split, stream);

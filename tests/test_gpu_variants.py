@@ -164,6 +164,28 @@ def test_bf16_edges_match_oracle(op):
         check_close(op, yd.cpu().numpy(), ref, a, tag, split=4)
 
 
+@pytest.mark.parametrize("shift", [1, 2, 4])
+def test_bf16_tensors_off_16_byte_addresses(shift):
+    op = _pw("off", 2, 72, 9, 7, 40)
+    x, w = make_inputs(op, "uniform", seed=46)
+    ref, a = reference(op, x, w)
+    xd, wd, yd = to_device(op, x, w)
+
+    def shifted(t):
+        u = torch.empty(t.numel() + shift, dtype=t.dtype, device=t.device)
+        u[shift:] = t.reshape(-1)
+        return u[shift:].reshape(t.shape)
+
+    space = L.ct_valid_space(op)
+    for xs, ws in ((shifted(xd), wd), (xd, shifted(wd)), (shifted(xd), shifted(wd))):
+        for s in random.Random(12).sample(space, 16):
+            tag = "%s by %d %s" % (op.name, shift, sched_str(s))
+            note(tag)
+            yd.fill_(float("nan"))
+            L.conv2d_run(op, s, xs, ws, yd)
+            check_close(op, yd.cpu().numpy(), ref, a, tag, split=4)
+
+
 def test_bf16_operand_beyond_2_gib():
     # x of 3.3 GB: byte offsets past 2^31, and the last pixels' reads end near the buffer's
     op = _pw("huge", 1, 960, 1280, 1343, 16)
