@@ -96,18 +96,18 @@ depthwise_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, f
   const int oh = bk.oh0 + td.rowg * RPT;  // first output row of the thread
 
   // buffers from the block's first plane (and filter) on
-  const int HW = H * W, OHW = a.OH * a.OW;
+  const unsigned HW = (unsigned)H * W, OHW = (unsigned)a.OH * a.OW;  // (part sums are unsigned)
   const int64_t plane0 = (int64_t)bk.n0 * C + bk.c0, planes = (int64_t)a.N * C - plane0;
   auto range = [](int64_t bytes) { return bytes < kPartOob ? bytes : (int64_t)kPartOob; };
   const float* xb = x + plane0 * HW;
   const __amdgpu_buffer_rsrc_t rx = make_rsrc(xb, range(planes * HW * 4));
   const __amdgpu_buffer_rsrc_t rwt = make_rsrc(w + (int64_t)bk.c0 * R * S, range((int64_t)(C - bk.c0) * R * S * 4));
-  const int wofs = live ? td.ci * R * S * 4 : kPartOob;
+  const unsigned wofs = part(live, (unsigned)td.ci * R * S);
 
   float wv[RC ? RC * RC : 1];
   if constexpr (RC != 0) {
 #pragma unroll
-    for (int r = 0; r < RC; ++r) bload3(rwt, wofs + r * 12, wv + r * 3);
+    for (int r = 0; r < RC; ++r) bload3(rwt, wofs + r * 12u, wv + r * 3);
   }
   float acc[RPT][VEC];
 #pragma unroll
@@ -137,13 +137,13 @@ depthwise_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, f
       const int p0 = qdiv(t, a.inv_plane), rem = t - p0 * plane;
       int hh = qdiv(rem, a.inv_iwt), ww = rem - hh * a.iw_t;
       int ni = qdiv(p0, a.inv_tc), ci = p0 - ni * a.tc;
-      int pofs = (ni * C + ci) * HW;
+      unsigned pofs = ((unsigned)ni * C + ci) * HW;
       const int n_left = a.N - bk.n0, c_left = C - bk.c0;
       const int wbase = wave_id() * 64;
       for (int e0 = 0; e0 < total; e0 += a.threads) {
         const int gh = ih_org + hh, gw = iw_org + ww;
         const bool ok = ni < n_left && ci < c_left && (unsigned)gh < (unsigned)H && (unsigned)gw < (unsigned)W;
-        if (e0 + t < total) copy_to_lds(rx, smem + e0 + wbase, ok ? (pofs + gh * W + gw) * 4 : kPartOob);
+        if (e0 + t < total) copy_to_lds(rx, smem + e0 + wbase, part(ok, pofs + (unsigned)gh * W + gw));
         ww += a.st_w;
         const bool k1 = ww >= a.iw_t;
         ww -= k1 ? a.iw_t : 0;
@@ -154,7 +154,7 @@ depthwise_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, f
         const bool k3 = ci >= a.tc;
         ci -= k3 ? a.tc : 0;
         ni += a.st_n + (k3 ? 1 : 0);
-        pofs += a.st_p + (k2 ? HW : 0) + (k3 ? (C - a.tc) * HW : 0);
+        pofs += a.st_p + (k2 ? HW : 0u) + (k3 ? (unsigned)(C - a.tc) * HW : 0u);
       }
       wait_copies();
     }
@@ -164,18 +164,18 @@ depthwise_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, f
   // operand (input row `row` of the thread's window rows, column `col`) sources:
   // LDS at (row, column) of the staged tile, or global at row and column offsets
   const float* xs = smem + (td.ni * a.tc + td.ci) * plane + td.rowg * RPT * sh * a.iw_t + td.colg * sw;
-  const int pofs = live ? (td.ni * C + td.ci) * HW * 4 : kPartOob;
+  const unsigned pofs = part(live, ((unsigned)td.ni * C + td.ci) * HW);
   const int ih0 = oh * sh - ph;
   if constexpr (RC != 0) {
     constexpr int NIN = (RPT - 1) * STC + RC;  // input rows of the thread's outputs
-    int cofs[VEC][RC];
+    unsigned cofs[VEC][RC];
     if constexpr (!LDS) {
 #pragma unroll
       for (int v = 0; v < VEC; ++v)
 #pragma unroll
         for (int s = 0; s < RC; ++s) {
           const int gw = (bk.ow0 + td.colg + v * a.cols) * STC - 1 + s;
-          cofs[v][s] = (unsigned)gw < (unsigned)W ? gw * 4 : kPartOob;
+          cofs[v][s] = part((unsigned)gw < (unsigned)W, gw);
         }
     }
 #pragma unroll
@@ -189,7 +189,7 @@ depthwise_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, f
           for (int s = 0; s < RC; ++s) xv[v][s] = xr[v * a.cols * STC + s];
       } else {
         const int gh = ih0 + i;
-        const int rofs = pofs + ((unsigned)gh < (unsigned)H ? gh * W * 4 : kPartOob);
+        const unsigned rofs = pofs + part((unsigned)gh < (unsigned)H, (unsigned)gh * W);
 #pragma unroll
         for (int v = 0; v < VEC; ++v)
 #pragma unroll
@@ -215,12 +215,12 @@ depthwise_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, f
         if constexpr (WIDE)
           wt = live ? w[((int64_t)c * R + r) * S + s] : 0.f;
         else
-          wt = bload1(rwt, wofs + (r * S + s) * 4);
+          wt = bload1(rwt, wofs + 4u * ((unsigned)r * S + s));
 #pragma unroll
         for (int u = 0; u < RPT; ++u) {
           const int gh = ih0 + u * sh + r * dh;
           const bool hok = (unsigned)gh < (unsigned)H;
-          const int rofs = pofs + (hok ? gh * W * 4 : kPartOob);
+          const unsigned rofs = pofs + part(hok, (unsigned)gh * W);
 #pragma unroll
           for (int v = 0; v < VEC; ++v) {
             const int gw = (bk.ow0 + td.colg + v * a.cols) * sw - pw + s * dw;
@@ -230,7 +230,7 @@ depthwise_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, f
             else if constexpr (WIDE)
               xv = load_or_zero(xc, (int64_t)gh * W + gw, live && hok && (unsigned)gw < (unsigned)W);
             else
-              xv = bload1(rx, rofs + ((unsigned)gw < (unsigned)W ? gw * 4 : kPartOob));
+              xv = bload1(rx, rofs + part((unsigned)gw < (unsigned)W, gw));
             acc[u][v] = fmaf(wt, xv, acc[u][v]);
           }
         }
@@ -252,14 +252,14 @@ depthwise_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, f
     }
   } else {
     const __amdgpu_buffer_rsrc_t ry = make_rsrc(y + plane0 * OHW, range(planes * OHW * 4));
-    const int yofs = live ? (td.ni * C + td.ci) * OHW * 4 : kPartOob;
+    const unsigned yofs = part(live, ((unsigned)td.ni * C + td.ci) * OHW);
 #pragma unroll
     for (int u = 0; u < RPT; ++u) {
-      const int rofs = yofs + (oh + u < a.OH ? (oh + u) * a.OW * 4 : kPartOob);
+      const unsigned rofs = yofs + part(oh + u < a.OH, (unsigned)(oh + u) * a.OW);
 #pragma unroll
       for (int v = 0; v < VEC; ++v) {
         const int ow = bk.ow0 + td.colg + v * a.cols;
-        bstore1(ry, rofs + (ow < a.OW ? ow * 4 : kPartOob), acc[u][v]);
+        bstore1(ry, rofs + part(ow < a.OW, ow), acc[u][v]);
       }
     }
   }

@@ -294,7 +294,7 @@ direct_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, floa
       const int hh = qdiv(rem, a.inv_pitch), ww = rem - hh * pitch;
       const int gh = ih_org + hh, gw = iw_org + ww;
       const bool ok = ww < a.iw_t && (unsigned)gh < (unsigned)H && (unsigned)gw < (unsigned)W;
-      return ok ? (gh * W + gw) * 4 : kOob;
+      return ok ? (unsigned)(gh * W + gw) * 4 : kOob;
     };
     auto w_off = [&](const int rem, const int k_left) {
       int i, j;  // channel of the group, word of its (channel, tap) run
@@ -305,7 +305,7 @@ direct_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, floa
         i = qdiv(rem, a.inv_wpc);
         j = rem - i * wrow;
       }
-      return j < a.ct * RS && i < min(MK, k_left) ? (i * C * RS + j) * 4 : kOob;
+      return j < a.ct * RS && i < min(MK, k_left) ? (unsigned)(i * C * RS + j) * 4 : kOob;
     };
     // Element e of the filter region (wt words, whole rows of `threads`) and
     // of the halo region goes to LDS word e of that region. Where both take at
@@ -325,18 +325,18 @@ direct_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, floa
     auto rsrc_w = [&](const int cc) { return make_rsrc(w + (int64_t)cc * RS, ((int64_t)K * C - cc) * RS * 4); };
     auto x_elem = [&](const int e) {
       const int c = qdiv(e, a.inv_plane);
-      const int o = x_off(e - c * plane);
-      return e < xt && o != kOob ? o + c * HW * 4 : kOob;
+      const unsigned o = x_off(e - c * plane);
+      return e < xt && o != kOob ? o + (unsigned)c * HW * 4 : kOob;
     };
     auto w_elem = [&](const int e) {
       const int kg = qdiv(e, a.inv_ks);
-      const int o = w_off(e - kg * a.ks, kg * MK < a.tk ? K - k0 - kg * MK : 0);
-      return o != kOob ? o + (k0 + kg * MK) * C * RS * 4 : kOob;
+      const unsigned o = w_off(e - kg * a.ks, kg * MK < a.tk ? K - k0 - kg * MK : 0);
+      return o != kOob ? o + (unsigned)(k0 + kg * MK) * C * RS * 4 : kOob;
     };
     auto staged = [&](auto ns) __attribute__((always_inline)) {
       constexpr int NS = decltype(ns)::value;
       // rows past the last one repeat it: same element, same LDS word
-      int off[NS];
+      unsigned off[NS];
       float val[NS];
 #pragma unroll
       for (int u = 0; u < NS; ++u) {
@@ -405,15 +405,17 @@ direct_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, floa
     // copies then take no vector instruction but themselves (lanes past a
     // region's end write zeros into its padding)
     constexpr int kPlan = DEEP ? 12 : 1;
-    int pw[kPlan], px[kPlan], npw = 0, npx = 0;
+    unsigned pw[kPlan], px[kPlan];
+    int npw = 0, npx = 0;
     const int gq = a.ks / 4, ng = min(a.tk / MK, (K - k0 + MK - 1) / MK);
     auto quad = [&](const int q) {  // byte offset of 16-byte quad q of a group's slice
       const int rq = wrow / 4, i = qdiv(q, a.inv_wq), j = q - i * rq;
-      return i < MK ? (i * C * RS + 4 * j) * 4 : kOob;
+      return i < MK ? ((unsigned)i * C * RS + 4 * j) * 4 : kOob;
     };
     auto flat_quad = [&](const int e) {  // and of the whole filter region
-      const int kg = qdiv(e, 4.f * a.inv_ks), o = quad(e - kg * gq);
-      return e < ng * gq && o != kOob ? o + kg * MK * C * RS * 4 : kOob;
+      const int kg = qdiv(e, 4.f * a.inv_ks);
+      const unsigned o = quad(e - kg * gq);
+      return e < ng * gq && o != kOob ? o + (unsigned)kg * MK * C * RS * 4 : kOob;
     };
     if constexpr (DEEP) {
       npw = (ng * gq + a.threads - 1) / a.threads;
@@ -451,7 +453,7 @@ direct_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, floa
         const int64_t left = ((int64_t)(K - k0) * C - cc) * RS;
         if (a.deep_w) {
           for (int q0 = 0; q0 < gq; q0 += a.threads) {
-            const int off = quad(q0 + t);
+            const unsigned off = quad(q0 + t);
             if (q0 + t < gq) {
 #pragma unroll 4
               for (int kg = 0; kg < ng; ++kg)
@@ -468,7 +470,7 @@ direct_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, floa
         const int64_t gstep = (int64_t)MK * C * RS;
         for (int e0 = 0; e0 < a.ks; e0 += a.threads) {
           // (rows past K lie past the buffer: the group's first row moves its base)
-          const int off = w_off(e0 + t, MK);
+          const unsigned off = w_off(e0 + t, MK);
           if (e0 + t < a.ks) {
             const float* base = w + ((int64_t)k0 * C + cc) * RS;
             int64_t left = ((int64_t)(K - k0) * C - cc) * RS;
@@ -489,7 +491,7 @@ direct_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, floa
       }
       if (a.deep_x) {
         for (int e0 = 0; e0 < plane; e0 += a.threads) {
-          const int off = x_off(e0 + t);
+          const unsigned off = x_off(e0 + t);
           if (e0 + t < plane) {
             const float* base = xn + (int64_t)cc * HW;
             float* dst = xs + e0 + wbase;
@@ -520,7 +522,7 @@ direct_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, floa
     constexpr int T = RC * RC;
     constexpr bool PT = RC == 3 && MW == 1;            // one resident offset per tap
     constexpr int NW = RC == 3 ? (MW - 1) * STC + 3 : MW;  // words of a unit's row
-    int xo[RC * (PT ? 3 : 1)];
+    unsigned xo[RC * (PT ? 3 : 1)];
     bool left = false, in[NW];
     {
       const int gw0 = ow * STC - RC / 2;
@@ -532,10 +534,10 @@ direct_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, floa
 #pragma unroll
           for (int s = 0; s < 3; ++s) {
             const int gw = gw0 + s;
-            xo[r * 3 + s] = hok && (unsigned)gw < (unsigned)W ? (gh * W + gw) * 4 : kOob;
+            xo[r * 3 + s] = hok && (unsigned)gw < (unsigned)W ? (unsigned)(gh * W + gw) * 4 : kOob;
           }
         } else {
-          xo[r] = hok && gw0 < W ? (gh * W + max(gw0, 0)) * 4 : kOob;
+          xo[r] = hok && gw0 < W ? (unsigned)(gh * W + max(gw0, 0)) * 4 : kOob;
         }
       }
       left = gw0 < 0;
@@ -548,7 +550,7 @@ direct_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, floa
         for (int s = 0; s < 3; ++s) v[s] = bload1(r, xo[row * 3 + s]);
       } else if constexpr (RC == 1 && STC == 2) {
 #pragma unroll
-        for (int j = 0; j < MW; ++j) v[j] = bload1(r, xo[0] + j * 8);
+        for (int j = 0; j < MW; ++j) v[j] = bload1(r, xo[0] + j * 8u);
       } else {
         bload_words<NW>(r, xo[row], v);
       }
@@ -574,9 +576,9 @@ direct_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, floa
     // the filter values are scalar loads, off the vector memory path, a unit
     // ahead of their use.
     const int kb = UNI ? __builtin_amdgcn_readfirstlane(kbase) : kbase;
-    int kofs[MK];
+    unsigned kofs[MK];
 #pragma unroll
-    for (int i = 0; i < MK; ++i) kofs[i] = min(kb + i, K - 1) * C * T * 4;
+    for (int i = 0; i < MK; ++i) kofs[i] = (unsigned)(min(kb + i, K - 1) * C * T) * 4;
     if constexpr (RC == 3) {
       // unit (channel u of DC, filter row r)
       constexpr int U = NW + (UNI ? 0 : 3 * MK);
@@ -589,7 +591,7 @@ direct_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, floa
         if constexpr (!UNI) {
           const __amdgpu_buffer_rsrc_t rw = rsrc_w(c_begin + c);
 #pragma unroll
-          for (int i = 0; i < MK; ++i) wv[i] = __builtin_amdgcn_raw_buffer_load_b96(rw, kofs[i] + r * 12, 0, 0);
+          for (int i = 0; i < MK; ++i) wv[i] = __builtin_amdgcn_raw_buffer_load_b96(rw, (int)(kofs[i] + r * 12u), 0, 0);
         }
       };
       // the scalar filter values of a unit (of the last channel past the range)
@@ -673,7 +675,7 @@ direct_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, floa
         if constexpr (!UNI) {
           const __amdgpu_buffer_rsrc_t rw = rsrc_w(c_begin + c);
 #pragma unroll
-          for (int i = 0; i < MK; ++i) wv[i] = __builtin_amdgcn_raw_buffer_load_b128(rw, kofs[i], 0, 0);
+          for (int i = 0; i < MK; ++i) wv[i] = __builtin_amdgcn_raw_buffer_load_b128(rw, (int)kofs[i], 0, 0);
         }
       };
       auto scalars = [&](const int c, float* v) __attribute__((always_inline)) {
@@ -733,25 +735,25 @@ direct_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, floa
     constexpr int NW = (MW - 1) * STC + SC;
     constexpr int U = NW + (UNI ? 0 : SC * MK), D0 = (kLimit - MK * MW - NW - MK - (UNI ? 52 : 40)) / U;
     constexpr int D1 = 56 / (NW + (UNI ? 0 : 2 * MK)), D2 = D0 < D1 ? D0 : D1, D = D2 < 1 ? 1 : (D2 > 4 ? 4 : D2);
-    int xo[NW], kofs[MK];
+    unsigned xo[NW], kofs[MK];
     const int kb = UNI ? __builtin_amdgcn_readfirstlane(kbase) : kbase;
 #pragma unroll
     for (int j = 0; j < NW; ++j) {
       const int gw = ow * STC - pw + j;
-      xo[j] = (unsigned)gw < (unsigned)W ? gw * 4 : kOob;
+      xo[j] = (unsigned)gw < (unsigned)W ? (unsigned)gw * 4 : kOob;
     }
 #pragma unroll
-    for (int i = 0; i < MK; ++i) kofs[i] = min(kb + i, K - 1) * C * RS * 4;
+    for (int i = 0; i < MK; ++i) kofs[i] = (unsigned)(min(kb + i, K - 1) * C * RS) * 4;
     const int gh0 = oh < a.OH ? oh * sh - ph : -R * dh;  // (every row outside)
     const int NU = (c_end - c_begin) * R;
     const int64_t wbytes = ((int64_t)K * C - c_begin) * RS * 4;
     float xq[D][NW], wq[D][SC * MK];
     auto load = [&](const int u, const int c, const int r, float* xv, float* wv) __attribute__((always_inline)) {
       const int gh = gh0 + r * dh;
-      const int ro = (unsigned)gh < (unsigned)H ? gh * W * 4 : kOob;
+      const unsigned ro = (unsigned)gh < (unsigned)H ? (unsigned)(gh * W) * 4 : kOob;
       const __amdgpu_buffer_rsrc_t rx = make_rsrc(xn + (int64_t)(c_begin + c) * HW, (int64_t)HW * 4);
 #pragma unroll
-      for (int j = 0; j < NW; ++j) xv[j] = bload1(rx, (int)((unsigned)ro + (unsigned)xo[j]));
+      for (int j = 0; j < NW; ++j) xv[j] = bload1(rx, ro + xo[j]);
       if constexpr (!UNI) {
         const int64_t at = (int64_t)u * SC * 4;
         const __amdgpu_buffer_rsrc_t rw = make_rsrc(w + (int64_t)c_begin * RS + (int64_t)u * SC, wbytes - at);
@@ -834,7 +836,7 @@ direct_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, floa
 #pragma unroll
                 for (int j = 0; j < MW; ++j) {
                   const int gw = (ow + j * cj) * sw - pw + s * dw;
-                  xv[u][j] = bload1(rx, hok && (unsigned)gw < (unsigned)W ? (xo + gh * W + gw) * 4 : kOob);
+                  xv[u][j] = bload1(rx, hok && (unsigned)gw < (unsigned)W ? (unsigned)(xo + gh * W + gw) * 4 : kOob);
                 }
 #pragma unroll
                 for (int i = 0; i < MK; ++i) wv[u][i] = wrow[i][co + r * S + s];

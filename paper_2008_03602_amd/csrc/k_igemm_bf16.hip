@@ -214,7 +214,7 @@ igemm_bf16_kernel(const unsigned short* __restrict__ x, const unsigned short* __
                 const int q = wave + (i << nw_shift);
                 unsigned o = off[i];
                 if constexpr (tail.value) o = k + 8 * col(q) < a.C ? o : kOobBytes;
-                copy16_to_lds(i < ca ? rx : rw, (float*)(dst + q * 512), (int)o);
+                copy16_to_lds(i < ca ? rx : rw, (float*)(dst + q * 512), o);
               }
           }
       };

@@ -20,19 +20,21 @@ __device__ __forceinline__ T load_or_zero(const T* __restrict__ p, int64_t idx, 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, int64_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, (int)bytes, 0x00020000);
 }
-constexpr int kOob = 0x7FFFFFF0;  // byte offset beyond every buffer: reads as 0
+// Byte offset beyond every buffer of the fp32 families: reads as 0. Offsets are unsigned,
+// since the words after it, or a second part outside, pass the largest int.
+constexpr unsigned kOob = 0x7FFFFFF0u;
 
 // One word at byte offset off of r (0 past the buffer's range).
-__device__ __forceinline__ float bload1(__amdgpu_buffer_rsrc_t r, int off) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
+__device__ __forceinline__ float bload1(__amdgpu_buffer_rsrc_t r, unsigned off) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
 }
 
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x3 __attribute__((ext_vector_type(3)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 // Three consecutive words at byte offset off (a multiple of 4) of r.
-__device__ __forceinline__ void bload3(__amdgpu_buffer_rsrc_t r, int off, float* v) {
-  const u32x3 q = __builtin_amdgcn_raw_buffer_load_b96(r, off, 0, 0);
+__device__ __forceinline__ void bload3(__amdgpu_buffer_rsrc_t r, unsigned off, float* v) {
+  const u32x3 q = __builtin_amdgcn_raw_buffer_load_b96(r, (int)off, 0, 0);
   const unsigned a = q.x, b = q.y, c = q.z;
   v[0] = __builtin_bit_cast(float, a);
   v[1] = __builtin_bit_cast(float, b);
@@ -41,9 +43,9 @@ __device__ __forceinline__ void bload3(__amdgpu_buffer_rsrc_t r, int off, float*
 // N consecutive words at byte offset off (a multiple of 4) of r, in loads of up to four
 // words; words past the buffer's range read 0.
 template <int N>
-__device__ __forceinline__ void bload_words(__amdgpu_buffer_rsrc_t r, int off, float* v) {
+__device__ __forceinline__ void bload_words(__amdgpu_buffer_rsrc_t r, unsigned off, float* v) {
   if constexpr (N >= 4) {
-    const u32x4 q = __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0);
+    const u32x4 q = __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0);
     const unsigned a = q.x, b = q.y, c = q.z, d = q.w;
     v[0] = __builtin_bit_cast(float, a);
     v[1] = __builtin_bit_cast(float, b);
@@ -53,7 +55,7 @@ __device__ __forceinline__ void bload_words(__amdgpu_buffer_rsrc_t r, int off, f
   } else if constexpr (N == 3) {
     bload3(r, off, v);
   } else if constexpr (N == 2) {
-    const u32x2 q = __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0);
+    const u32x2 q = __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0);
     const unsigned a = q.x, b = q.y;
     v[0] = __builtin_bit_cast(float, a);
     v[1] = __builtin_bit_cast(float, b);
@@ -61,26 +63,29 @@ __device__ __forceinline__ void bload_words(__amdgpu_buffer_rsrc_t r, int off, f
     v[0] = bload1(r, off);
   }
 }
-__device__ __forceinline__ void bstore1(__amdgpu_buffer_rsrc_t r, int off, float v) {
-  __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, off, 0, 0);
+__device__ __forceinline__ void bstore1(__amdgpu_buffer_rsrc_t r, unsigned off, float v) {
+  __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, (int)off, 0, 0);
 }
 
-// Offsets that are sums of up to three parts (plane, row, column), each of which may be
-// out of range on its own: buffers of at most kPartOob bytes, and kPartOob for a part
+// Byte offsets that are sums of up to three parts (plane, row, column), each of which may
+// be outside on its own: buffers of at most kPartOob bytes, and kPartOob for a part
 // outside. Any sum with such a part is then past the buffer, and three of them (plus an
-// instruction's immediate) stay below 2^32.
-constexpr int kPartOob = 0x3FFFFFF0;
+// instruction's immediate) stay below 2^32. The parts are unsigned: three outside exceed
+// the largest int.
+constexpr unsigned kPartOob = 0x3FFFFFF0u;
+// The part of `words` words (below kPartOob bytes where it is inside, anything elsewhere).
+constexpr unsigned part(bool inside, unsigned words) { return inside ? 4u * words : kPartOob; }
 
 typedef __attribute__((address_space(3))) void lds_void_t;
 // One wave instruction: lane i copies the word at byte offset off of r to
 // lds[i] (an inactive lane copies nothing), without a trip through registers.
-__device__ __forceinline__ void copy_to_lds(__amdgpu_buffer_rsrc_t r, float* lds, int off) {
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void_t*)lds, 4, off, 0, 0, 0);
+__device__ __forceinline__ void copy_to_lds(__amdgpu_buffer_rsrc_t r, float* lds, unsigned off) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void_t*)lds, 4, (int)off, 0, 0, 0);
 }
 // The same with 16 bytes per lane: lane i fills lds[4i .. 4i+3] (lds and the
 // lane's source 16-byte aligned).
-__device__ __forceinline__ void copy16_to_lds(__amdgpu_buffer_rsrc_t r, float* lds, int off) {
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void_t*)lds, 16, off, 0, 0, 0);
+__device__ __forceinline__ void copy16_to_lds(__amdgpu_buffer_rsrc_t r, float* lds, unsigned off) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void_t*)lds, 16, (int)off, 0, 0, 0);
 }
 // Waits for this wave's copies to land in LDS.
 __device__ __forceinline__ void wait_copies() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
