@@ -24,6 +24,12 @@ constexpr int kBf16GroupBytes = 40 << 10;
 // steps of 5 and more fragments, 80 to 128 registers: 0.99 times as fast as 2)
 constexpr int bf16_most_steps(int frags) { return frags <= 2 ? 8 : frags <= 4 ? 4 : 2; }
 constexpr int kMaxLoadsPerThread = 8;     // register staging bound of the GEMM loaders
+// Byte offsets of a depthwise block are sums of up to three parts (plane, row, column),
+// each of which may be outside on its own: buffers of at most kPartOob bytes, and kPartOob
+// for a part outside. Any sum with such a part is then past the buffer, and three of them
+// (plus an instruction's immediate) stay below 2^32. The parts are unsigned: three outside
+// exceed the largest int.
+constexpr unsigned kPartOob = 0x3FFFFFF0u;
 // fp32 MFMA family, stages 3 (four loader waves): the largest accumulator
 // tile in registers that still leaves room, two waves per SIMD, for the copy
 // plan the loaders keep across the chunk loop (no spills up to here)
@@ -94,6 +100,7 @@ struct Geom {
   // family-specific derived values
   int64_t tiles_h, tiles_w, tiles_k, tiles_c, tiles_n;  // grid factors
   int ih_t, iw_t;     // input halo tile (direct, depthwise)
+  int dw_wide;        // depthwise: a block's planes or filters span more than part offsets reach
   int d_alt;          // direct family: the ALT variant (k_direct.inc.h)
   int d_pitch, d_wpc, d_ks, d_wt;  // direct family, LDS words: halo row; filter per output channel, per group of MK, all
   int bm, bn;         // GEMM block tile (rows x cols)

@@ -75,7 +75,7 @@ __device__ __forceinline__ DwThread dw_thread(const DwArgs& a) {
 // indices. Measured on MobileNet-v2 b16's 10 layers and a ragged one, the mean over
 // 160 sampled schedules each, against divisions, 64-bit addresses and strided rows: 30.5
 // to 18.7 us on the whole GPU, 102 to 56 us on a quarter.
-// WIDE: a block whose planes span more than 32-bit part offsets reach (kPartOob bytes);
+// WIDE: a block whose planes span more than 32-bit part offsets reach (geom_depthwise);
 // only the generic filter path has that variant.
 template <int VEC, int RPT, bool LDS, int SPEC, bool WIDE>
 __global__ void __launch_bounds__(dw_max_threads(VEC * RPT))
@@ -417,13 +417,8 @@ int launch_depthwise_f32(const OpX& x, const ct_schedule& s, const Geom& g, cons
   a.st_h = a.threads % plane / a.iw_t;
   a.st_c = a.threads / plane % a.tc;
   a.st_n = a.threads / plane / a.tc;
-  // a block's planes, rows and columns are addressed by 32-bit part offsets where they
-  // (and the staging counters' run past them) stay in that range; else the wide variant
-  const int64_t hw = (int64_t)a.H * a.W, ohw = (int64_t)a.OH * a.OW;
-  const int64_t span = ((int64_t)a.nb * a.C + a.tc) * (hw > ohw ? hw : ohw);
-  const bool wide = 4 * span >= kPartOob || 4 * (int64_t)a.tc * a.R * a.S >= kPartOob;
   // (a step of nb images or more ends the staging loop: its offset is not used)
-  a.st_p = wide || a.st_n >= a.nb ? 0 : (a.st_n * a.C + a.st_c) * (int)hw;
+  a.st_p = !s.knob[LDS] || g.dw_wide || a.st_n >= a.nb ? 0 : (a.st_n * a.C + a.st_c) * a.H * a.W;
   // the 3x3 specialisation needs pad 1 and dilation 1, which op_spec checks
   DwFn fn;
   if (s.knob[Q4]) {  // the validator admits it for 3x3 pad-1 ops (spec 3 or 4) with VEC = 4, LDS = 0
@@ -433,7 +428,7 @@ int launch_depthwise_f32(const OpX& x, const ct_schedule& s, const Geom& g, cons
     fn = st == 2 ? dw_q4_pick<2>(s.knob[RPT]) : dw_q4_pick<1>(s.knob[RPT]);
   } else {
     a.vec_ld = a.vec_st = 0;
-    fn = dw_pick(s.knob[VEC], s.knob[RPT], s.knob[LDS], g.spec, wide);
+    fn = dw_pick(s.knob[VEC], s.knob[RPT], s.knob[LDS], g.spec, g.dw_wide);
   }
   hipLaunchKernelGGL(fn, dim3((unsigned)g.blocks), dim3(g.threads), g.lds_bytes, (hipStream_t)stream,
                      (const float*)xin, (const float*)w, (float*)y, a);

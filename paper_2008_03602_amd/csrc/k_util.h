@@ -2,6 +2,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include "ct_internal.h"
+
 namespace ct {
 
 // Bounds-checked load without a branch: the address is clamped to element 0
@@ -67,13 +69,8 @@ __device__ __forceinline__ void bstore1(__amdgpu_buffer_rsrc_t r, unsigned off, 
   __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, (int)off, 0, 0);
 }
 
-// Byte offsets that are sums of up to three parts (plane, row, column), each of which may
-// be outside on its own: buffers of at most kPartOob bytes, and kPartOob for a part
-// outside. Any sum with such a part is then past the buffer, and three of them (plus an
-// instruction's immediate) stay below 2^32. The parts are unsigned: three outside exceed
-// the largest int.
-constexpr unsigned kPartOob = 0x3FFFFFF0u;
-// The part of `words` words (below kPartOob bytes where it is inside, anything elsewhere).
+// An offset part (kPartOob) of `words` words: below kPartOob bytes where it is inside,
+// anything elsewhere.
 constexpr unsigned part(bool inside, unsigned words) { return inside ? 4u * words : kPartOob; }
 
 typedef __attribute__((address_space(3))) void lds_void_t;
