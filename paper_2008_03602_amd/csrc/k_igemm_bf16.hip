@@ -252,12 +252,6 @@ igemm_bf16_kernel(const unsigned short* __restrict__ x, const unsigned short* __
 #pragma unroll
         for (int st = 1; st < KC / KSTEP; ++st)
           if (st * KSTEP < left) mma_step(src, st);
-        // A copy of the accumulators at this loop's end has come without the
-        // wait that a matrix result needs (two of the first four of a lane
-        // were stale): wait here, 18 cycles a chunk.
-        __builtin_amdgcn_sched_barrier(0);
-        asm volatile("s_nop 15\n\ts_nop 1" :::);
-        __builtin_amdgcn_sched_barrier(0);
       }
     }
   }
