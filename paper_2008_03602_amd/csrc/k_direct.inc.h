@@ -320,7 +320,8 @@ direct_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, floa
     // MACs never read. kMaxNs is what fits beside the accumulators and the
     // units in flight.
     const int xt = a.ct * plane, wt = a.wt;
-    const int nsx = (xt + a.threads - 1) / a.threads, nsw = (wt + a.threads - 1) / a.threads, nst = nsw + nsx;
+    auto rows = [&](const int words) { return __builtin_amdgcn_readfirstlane((words + a.threads - 1) / a.threads); };
+    const int nsx = rows(xt), nsw = rows(wt), nst = nsw + nsx;
     auto rsrc_x = [&](const int cc) { return make_rsrc(xn + (int64_t)cc * HW, (int64_t)(C - cc) * HW * 4); };
     auto rsrc_w = [&](const int cc) { return make_rsrc(w + (int64_t)cc * RS, ((int64_t)K * C - cc) * RS * 4); };
     auto x_elem = [&](const int e) {
@@ -398,13 +399,19 @@ direct_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, floa
     // by plane and only the scalar base moves between them: one offset per
     // lane, not one per copy (about 28 vector instructions). (Batches of 16
     // loads through registers instead took 1.2 times as long over the sampled
-    // LDS schedules.)
+    // LDS schedules.) The loops over planes and groups are not unrolled: what
+    // four copies at a time kept across chunks went through vector lanes, also
+    // in the kernels that never come here (1600 sampled LDS schedules of
+    // ResNet-18 and ragged layers: 58.3 ms, and 54.2 ms with one at a time and
+    // the plan's bounds opaque).
     const int wbase = wave_id() * 64;
     // DEEP: the lane offsets of up to kPlan 16-byte filter copies and kPlan
     // halo copies are the same in every chunk and stay in registers: a chunk's
     // copies then take no vector instruction but themselves (lanes past a
-    // region's end write zeros into its padding)
-    constexpr int kPlan = DEEP ? 12 : 1;
+    // region's end write zeros into its padding). kPlan is what fits beside the
+    // accumulators and the units in flight, so that nothing goes to scratch.
+    constexpr int kRoom = (kLimit - MK * MW - (SC ? D * (NW + WW) : 24) - 56) / 2;
+    constexpr int kPlan = !DEEP ? 1 : (kRoom < 4 ? 4 : (kRoom < 12 ? kRoom : 12));
     unsigned pw[kPlan], px[kPlan];
     int npw = 0, npx = 0;
     const int gq = a.ks / 4, ng = min(a.tk / MK, (K - k0 + MK - 1) / MK);
@@ -418,7 +425,7 @@ direct_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, floa
       return e < ng * gq && o != kOob ? o + (unsigned)kg * MK * C * RS * 4 : kOob;
     };
     if constexpr (DEEP) {
-      npw = (ng * gq + a.threads - 1) / a.threads;
+      npw = rows(ng * gq);
       npx = nsx;
       if (a.vec_w && npw <= kPlan && npx <= kPlan) {
 #pragma unroll
@@ -435,19 +442,25 @@ direct_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, floa
       if (DEEP && npw) {
         const __amdgpu_buffer_rsrc_t rw =
             make_rsrc(w + ((int64_t)k0 * C + cc) * RS, ((int64_t)(K - k0) * C - cc) * RS * 4), rx = rsrc_x(cc);
+        // opaque here, so that the comparisons and LDS addresses are made where they
+        // are used rather than kept in scalar registers, which do not suffice
+        int cw = npw, cx = npx, row = a.threads;
+        asm volatile("" : "+s"(cw), "+s"(cx), "+s"(row));
 #pragma unroll
-        for (int u = 0; u < kPlan; ++u)
-          if (u < npw) copy16_to_lds(rw, smem + 4 * (u * a.threads + wbase), pw[u]);
+        for (int u0 = 0; u0 < kPlan; u0 += 4)
+          if (u0 < cw) {
 #pragma unroll
-        for (int u = 0; u < kPlan; ++u)
-          if (u < npx) copy_to_lds(rx, xs + u * a.threads + wbase, px[u]);
-        wait_copies();
-        __syncthreads();
-        compute(nc);
-        __syncthreads();
-        continue;
-      }
-      if (DEEP && a.vec_w) {
+            for (int u = u0; u < u0 + 4 && u < kPlan; ++u)
+              if (u < cw) copy16_to_lds(rw, smem + 4 * (u * row + wbase), pw[u]);
+          }
+#pragma unroll
+        for (int u0 = 0; u0 < kPlan; u0 += 4)
+          if (u0 < cx) {
+#pragma unroll
+            for (int u = u0; u < u0 + 4 && u < kPlan; ++u)
+              if (u < cx) copy_to_lds(rx, xs + u * row + wbase, px[u]);
+          }
+      } else if (DEEP && a.vec_w) {
         const int64_t gstep = (int64_t)MK * C * RS;
         const float* base = w + ((int64_t)k0 * C + cc) * RS;
         const int64_t left = ((int64_t)(K - k0) * C - cc) * RS;
@@ -455,7 +468,7 @@ direct_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, floa
           for (int q0 = 0; q0 < gq; q0 += a.threads) {
             const unsigned off = quad(q0 + t);
             if (q0 + t < gq) {
-#pragma unroll 4
+#pragma unroll 1
               for (int kg = 0; kg < ng; ++kg)
                 copy16_to_lds(make_rsrc(base + kg * gstep, (left - kg * gstep) * 4),
                               smem + kg * a.ks + 4 * (q0 + wbase), off);
@@ -475,7 +488,7 @@ direct_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, floa
             const float* base = w + ((int64_t)k0 * C + cc) * RS;
             int64_t left = ((int64_t)(K - k0) * C - cc) * RS;
             float* dst = smem + e0 + wbase;
-#pragma unroll 4
+#pragma unroll 1
             for (int kg = 0; kg < ng; ++kg) {
               copy_to_lds(make_rsrc(base, left * 4), dst, off);
               base += gstep;
@@ -489,13 +502,14 @@ direct_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, floa
         for (int e0 = 0; e0 < wt; e0 += a.threads)
           if (e0 + t < wt) copy_to_lds(rwc, smem + e0 + wbase, w_elem(e0 + t));
       }
-      if (a.deep_x) {
+      if (DEEP && npw) {  // (copied above)
+      } else if (a.deep_x) {
         for (int e0 = 0; e0 < plane; e0 += a.threads) {
           const unsigned off = x_off(e0 + t);
           if (e0 + t < plane) {
             const float* base = xn + (int64_t)cc * HW;
             float* dst = xs + e0 + wbase;
-#pragma unroll 4
+#pragma unroll 1
             for (int c = 0; c < nc; ++c) {
               copy_to_lds(make_rsrc(base, (int64_t)HW * 4), dst, off);
               base += HW;
@@ -733,7 +747,7 @@ direct_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, floa
     // row plus a column offset; either part outside the image sends the sum
     // past the buffer.
     constexpr int NW = (MW - 1) * STC + SC;
-    constexpr int U = NW + (UNI ? 0 : SC * MK), D0 = (kLimit - MK * MW - NW - MK - (UNI ? 52 : 40)) / U;
+    constexpr int U = NW + (UNI ? 0 : SC * MK), D0 = (kLimit - MK * MW - NW - MK - (UNI ? 60 : 40)) / U;
     constexpr int D1 = 56 / (NW + (UNI ? 0 : 2 * MK)), D2 = D0 < D1 ? D0 : D1, D = D2 < 1 ? 1 : (D2 > 4 ? 4 : D2);
     unsigned xo[NW], kofs[MK];
     const int kb = UNI ? __builtin_amdgcn_readfirstlane(kbase) : kbase;
