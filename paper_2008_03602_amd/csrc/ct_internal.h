@@ -101,7 +101,7 @@ struct Geom {
   int64_t tiles_h, tiles_w, tiles_k, tiles_c, tiles_n;  // grid factors
   int ih_t, iw_t;     // input halo tile (direct, depthwise)
   int dw_wide;        // depthwise: a block's planes or filters span more than part offsets reach
-  int d_alt;          // direct family: the ALT variant (k_direct.inc.h)
+  int d_alt;          // direct family: the ALT variant (k_direct.inc.h; generic: rows of 4 taps and more)
   int d_pitch, d_wpc, d_ks, d_wt;  // direct family, LDS words: halo row; filter per output channel, per group of MK, all
   int bm, bn;         // GEMM block tile (rows x cols)
   int chunks;         // reduction chunks in total

@@ -16,7 +16,8 @@
 // 1 s1/s2, filters of 5 or 7 columns with column stride 1 or 2 and no column
 // dilation, generic) and ALT: without LDS, scalar filter loads where every wave
 // lies inside one channel group; with LDS, the variant for chunks too deep for
-// registers whose filter rows are whole 16-byte quads. Runtime: tiles, CT, SPLIT.
+// registers whose filter rows are whole 16-byte quads, or in the generic path
+// the one for filter rows of four taps and more. Runtime: tiles, CT, SPLIT.
 //
 // What bounds it, and the layouts that follow. The operand traffic per
 // multiply-add, not the multiply-adds: with one 4-byte LDS read per operand a
@@ -116,7 +117,7 @@ direct_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, floa
   const int ph = RC ? RC / 2 : a.ph, pw = RC ? RC / 2 : a.pw;
   const int RS = R * S;
   const int C = a.C, H = a.H, W = a.W, K = a.K;
-  constexpr bool UNI = ALT && !LDS, DEEP = ALT && LDS;
+  constexpr bool UNI = ALT && !LDS, DEEP = ALT && LDS && SPEC != 0;
   constexpr int kLimit = direct_max_threads(MK * MW) >= 1024 ? 128 : 256;  // registers per thread
 
   extern __shared__ __align__(16) float smem[];
@@ -265,22 +266,40 @@ direct_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, floa
           }
         }
       } else {
-#pragma unroll UNR
+        // ALT: the taps of a filter row in groups of G (by the unroll knob; 2 where four
+        // taps of 8 channels exceed 128 registers), all of a group's reads before its
+        // multiply-adds: a tap at a time waits out an LDS latency each. Shorter rows run
+        // without, in kernels of their own: with both in one, their registers cost the
+        // short rows 3 to 10 %. 80 sampled LDS schedules each of a 9 x 9, an 11 x 11 and
+        // a 4 x 4 filter: 2924 to 2498 us, 3044 to 2856, 2935 to 2643.
+        constexpr int G = ALT ? (UNR == 1 || (MK == 8 && kLimit == 128) ? 2 : 4) : 1, kUnr = ALT ? 1 : UNR;
+        auto taps = [&](auto count, const float* xr, const float* wr) __attribute__((always_inline)) {
+          constexpr int N = decltype(count)::value;
+          float xv[N][MW], wv[N][MK];
+#pragma unroll
+          for (int u = 0; u < N; ++u) {
+#pragma unroll
+            for (int j = 0; j < MW; ++j) xv[u][j] = xr[j * cj * sw + u * dw];
+#pragma unroll
+            for (int i = 0; i < MK; ++i) wv[u][i] = wr[i * wrow + u];
+          }
+#pragma unroll
+          for (int u = 0; u < N; ++u)
+#pragma unroll
+            for (int i = 0; i < MK; ++i)
+#pragma unroll
+              for (int j = 0; j < MW; ++j) acc[i][j] = fmaf(wv[u][i], xv[u][j], acc[i][j]);
+        };
+#pragma unroll kUnr
         for (int c = 0; c < nc; ++c) {
           const float* xr = xthr + c * plane;
           const float* wr = wsm + c * RS;
           for (int r = 0; r < R; ++r) {
-            for (int s = 0; s < S; ++s) {
-              float xv[MW], wv[MK];
-#pragma unroll
-              for (int j = 0; j < MW; ++j) xv[j] = xr[(r * dh) * pitch + j * cj * sw + s * dw];
-#pragma unroll
-              for (int i = 0; i < MK; ++i) wv[i] = wr[i * wrow + r * S + s];
-#pragma unroll
-              for (int i = 0; i < MK; ++i)
-#pragma unroll
-                for (int j = 0; j < MW; ++j) acc[i][j] = fmaf(wv[i], xv[j], acc[i][j]);
-            }
+            int s = 0;
+            if constexpr (G > 1)
+              for (; s + G <= S; s += G)
+                taps(std::integral_constant<int, G>{}, xr + r * dh * pitch + s * dw, wr + r * S + s);
+            for (; s < S; ++s) taps(std::integral_constant<int, 1>{}, xr + r * dh * pitch + s * dw, wr + r * S + s);
           }
         }
       }
@@ -905,15 +924,19 @@ direct_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, floa
 using DirectFn = void (*)(const float*, const float*, float*, DirectArgs);
 
 
-// The unroll knob is the generic paths' only, ALT the others'.
+// The unroll knob is the generic paths' only; those without LDS have no ALT variant.
 template <int MK, int MW, bool LDS, int SPEC>
 static DirectFn pick_unr(int unr, bool alt) {
-  if constexpr (SPEC == 0)
-    return unr == 2 ? (DirectFn)direct_f32_kernel<MK, MW, LDS, SPEC, 2, false>
-                    : (DirectFn)direct_f32_kernel<MK, MW, LDS, SPEC, 1, false>;
-  else
+  if constexpr (SPEC != 0) {
     return alt ? (DirectFn)direct_f32_kernel<MK, MW, LDS, SPEC, 1, true>
                : (DirectFn)direct_f32_kernel<MK, MW, LDS, SPEC, 1, false>;
+  } else {
+    if (LDS && alt)
+      return unr == 2 ? (DirectFn)direct_f32_kernel<MK, MW, LDS, SPEC, 2, LDS>
+                      : (DirectFn)direct_f32_kernel<MK, MW, LDS, SPEC, 1, LDS>;
+    return unr == 2 ? (DirectFn)direct_f32_kernel<MK, MW, LDS, SPEC, 2, false>
+                    : (DirectFn)direct_f32_kernel<MK, MW, LDS, SPEC, 1, false>;
+  }
 }
 template <int MK, int MW, bool LDS>
 static DirectFn pick_spec(int spec, int unr, bool alt) {

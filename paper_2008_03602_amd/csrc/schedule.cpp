@@ -217,7 +217,7 @@ static int64_t direct_lds_layout(const OpX& x, const ct_schedule& s, int64_t thr
       g->spec = SPEC_GENERIC;
       continue;
     }
-    g->d_alt = alt && rows;
+    g->d_alt = padded ? alt && rows : o.s >= 4;
     g->d_pitch = (int)pitch;
     g->d_wpc = (int)wpc;
     g->d_ks = (int)ks;

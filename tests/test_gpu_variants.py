@@ -54,7 +54,8 @@ def _f32(name, n, c, h, w, k, r, s, stride, pad):
 
 # direct family: channel counts below and off the ring's depth, windows wider than the
 # image, both strides of the 5- and 7-column paths with uneven padding and rectangular
-# filters, and shapes that stay on the generic path
+# filters, and shapes that stay on the generic path, with rows of fewer than four taps and
+# of one, two and more groups of them
 DIRECT_EDGES = [
     _f32("c1", 2, 1, 5, 6, 9, 3, 3, 1, (1, 1)),
     _f32("c13", 1, 13, 6, 3, 10, 3, 3, 2, (1, 1)),
@@ -67,6 +68,9 @@ DIRECT_EDGES = [
     _f32("rect2x5", 1, 9, 7, 12, 8, 2, 5, 1, (1, 0)),
     _f32("rect3x7s2", 2, 5, 9, 16, 8, 3, 7, 2, (0, 4)),
     _f32("f4", 1, 5, 9, 10, 8, 4, 4, 1, (1, 1)),
+    _f32("f6s2", 2, 3, 15, 13, 12, 6, 6, 2, (2, 2)),
+    _f32("row9", 1, 4, 7, 17, 9, 2, 9, 1, (0, 4)),
+    W.Op("dil2x11", 1, 3, 9, 34, 8, 3, 11, 1, 1, 1, 10, 1, 2, 1, 0, 0),
     W.Op("dilh5", 1, 4, 14, 10, 8, 3, 5, 1, 1, 2, 2, 2, 1, 1, 0, 0),
 ]
 
@@ -77,10 +81,10 @@ def test_direct_edges_match_oracle(op):
     ref, a = reference(op, x, w)
     xd, wd, yd = to_device(op, x, w)
     space = [s for s in L.ct_valid_space(op) if s.family == W.FAM_DIRECT_F32]
-    # one schedule of every (mk, mw, lds), then a sample
+    # one schedule of every kernel, then a sample
     by = {}
     for s in random.Random(8).sample(space, len(space)):
-        by.setdefault((s.knob[3], s.knob[4], s.knob[5]), s)
+        by.setdefault(L.ct_kernel_name(op, s), s)
     for s in list(by.values()) + random.Random(9).sample(space, min(40, len(space))):
         tag = "%s %s" % (op.name, sched_str(s))
         note(tag)

@@ -19,6 +19,7 @@ OPS = W.resnet18() + W.mobilenet_v2_depthwise(16) + W.mobilenet_v2_pointwise(16)
     _f32("f5s2", 24, 28, 48, 5, 5, 2, 2),
     _f32("f7s1", 16, 28, 32, 7, 7, 1, 3),
     _f32("f4", 32, 28, 64, 4, 4, 1, 1),
+    _f32("f2", 32, 28, 64, 2, 2, 1, 0),
     _f32("dil", 32, 28, 64, 3, 3, 1, 2, dil=2),
     _f32("dw5", 32, 28, 32, 5, 5, 1, 2, groups=32),
     # blocks whose planes span more than 2^30 bytes, fixed filters and another one
