@@ -88,6 +88,36 @@ constexpr int direct_spec_s(int spec) {
 constexpr int direct_spec_stride(int spec) { return spec == 0 ? 0 : (spec % 2 ? 1 : 2); }
 Spec op_spec(const OpX& x);
 
+// Threads per block that leave registers for a direct accumulator tile of mk x mw and its
+// operands without spilling.
+constexpr int direct_max_threads(int tile) { return tile >= 16 ? 512 : 1024; }
+
+// What the registers of a direct instance with LDS hold beside its accumulators.
+// Load units of the compute loop: a filter row of one channel, or four channels of a 1x1
+// filter. `ring` units stay in flight, so that the LDS latency of a unit passes behind the
+// multiply-adds of those before it: 2 where a unit's multiply-adds take longer than the
+// latency, up to 4 where they are short, fewer where the registers end. `staged`: words
+// per thread that a chunk may have to go through registers.
+struct DirectRegs {
+  int limit;           // registers per thread
+  int x_words, w_words;  // operand words of a unit
+  int ring, staged;
+};
+constexpr DirectRegs direct_regs(int mk, int mw, int spec) {
+  const int sc = direct_spec_s(spec), stc = direct_spec_stride(spec);
+  DirectRegs r = {};
+  r.limit = direct_max_threads(mk * mw) >= 1024 ? 128 : 256;
+  r.x_words = sc == 1 ? 4 * mw : (sc ? (mw - 1) * stc + sc : 1);
+  r.w_words = sc == 1 ? 4 * mk : (sc ? sc * mk : 1);
+  const int unit = r.x_words + r.w_words, clocks = sc == 1 ? 16 * mk * mw : 4 * sc * mk * mw;
+  const int fit = (r.limit - mk * mw - 72) / unit;
+  const int want = clocks >= 160 ? 2 : (clocks >= 48 || sc == 1 ? 3 : 4);
+  r.ring = fit < 1 ? 1 : (fit < want ? fit : want);
+  const int words = (r.limit - mk * mw - (sc ? r.ring * unit : 24) - (sc == 1 ? 60 : 44)) / 2;
+  r.staged = words >= 24 && r.limit == 256 ? 24 : (words >= 16 ? 16 : (words >= 12 ? 12 : (words >= 8 ? 8 : 6)));
+  return r;
+}
+
 struct Geom {
   int family;
   Spec spec;

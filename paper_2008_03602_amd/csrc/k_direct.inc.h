@@ -73,10 +73,6 @@ struct DirectArgs {
   int64_t ny;
 };
 
-// Threads per block that leave registers for an MK x MW accumulator tile
-// and its operands without spilling.
-__host__ __device__ constexpr int direct_max_threads(int tile) { return tile >= 16 ? 512 : 1024; }
-
 __host__ __device__ constexpr int spec_r(int spec) { return spec == 1 || spec == 2 ? 1 : (spec == 3 || spec == 4 ? 3 : 0); }
 
 typedef float f32x2d __attribute__((ext_vector_type(2)));
@@ -155,18 +151,10 @@ direct_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, floa
     const int pitch = a.pitch, plane = a.ih_t * pitch;
     const float* xthr = xs + lr * sh * pitch + (CONSEC ? lc * MW : lc) * sw;
 
-    // Load units of the compute loop: a filter row of one channel, or four
-    // channels of a 1x1 filter. D units stay in flight, so that the LDS
-    // latency of a unit passes behind the multiply-adds of the D before it:
-    // 2 where a unit's multiply-adds take longer than the latency, up to 4
-    // where they are short, fewer where the registers end.
-    constexpr int NW = SC == 1 ? 4 * MW : (SC ? (MW - 1) * STC + SC : 1);  // operand words of a unit
-    constexpr int WW = SC == 1 ? 4 * MK : (SC ? SC * MK : 1);
+    // Units of the compute loop, and how many stay in flight (direct_regs)
+    constexpr DirectRegs kHeld = direct_regs(MK, MW, SPEC);
+    constexpr int NW = kHeld.x_words, WW = kHeld.w_words, D = kHeld.ring;
     constexpr int WA = MK % 4 == 0 ? 4 : MK;
-    constexpr int kClk = SC == 1 ? 16 * MK * MW : 4 * SC * MK * MW;
-    constexpr int kFit = (kLimit - MK * MW - 72) / (NW + WW);
-    constexpr int kWant = kClk >= 160 ? 2 : (kClk >= 48 || SC == 1 ? 3 : 4);
-    constexpr int D = kFit < 1 ? 1 : (kFit < kWant ? kFit : kWant);
     auto compute = [&](const int nc) __attribute__((always_inline)) {
       if constexpr (SC != 0) {
         constexpr int XA = MW * STC % 4 == 0 ? 4 : (MW * STC % 2 == 0 ? 2 : 1);
@@ -382,8 +370,7 @@ direct_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, floa
         __syncthreads();  // the next chunk's stores overwrite the tiles
       }
     };
-    constexpr int kNs = (kLimit - MK * MW - (SC ? D * (NW + WW) : 24) - (SC == 1 ? 60 : 44)) / 2;
-    constexpr int kMaxNs = kNs >= 24 && kLimit == 256 ? 24 : (kNs >= 16 ? 16 : (kNs >= 12 ? 12 : (kNs >= 8 ? 8 : 6)));
+    constexpr int kMaxNs = kHeld.staged;
     const bool done = !DEEP && nst <= kMaxNs;
     if constexpr (!DEEP) {
       if (nst <= 2) {

@@ -188,9 +188,11 @@ static bool split_ok(int64_t chunks, int split, int64_t* cps) {
 // to be staged through registers always do). Where the padded tile exceeds the
 // LDS, the generic path runs with unpadded rows and slices, which the caller
 // has checked to fit. The ALT variant takes chunks of more words per thread
-// than its 128- or 256-register instances stage through registers (16, or 24
-// beside 16 or more accumulators), if their filter rows are whole 16-byte quads. Returns the bytes; sets g->spec, g->d_alt
-// and the pitches.
+// than the instance stages through registers (direct_regs: 6 to 24; a line at
+// 16 and 24 for all left those between to copies without a plan, 1.7 times as
+// slow on 1x1 stride-2 schedules), if their filter rows are whole 16-byte
+// quads; in the generic path it is the variant for long filter rows. Returns
+// the bytes; sets g->spec, g->d_alt and the pitches.
 static int64_t direct_lds_layout(const OpX& x, const ct_schedule& s, int64_t threads, Geom* g) {
   using namespace direct_knob;
   const ct_op& o = x.op;
@@ -209,7 +211,7 @@ static int64_t direct_lds_layout(const OpX& x, const ct_schedule& s, int64_t thr
     const int64_t w0 = groups * ks, x0 = ct * g->ih_t * pitch;
     int64_t wr = cdiv(w0, threads) * threads;
     const int64_t xr = cdiv(x0, threads) * threads;
-    const bool alt = padded && wr + xr > (mk * mw >= 16 ? 24 : 16) * threads && wpc % 4 == 0 && x.kred % 4 == 0;
+    const bool alt = padded && wr + xr > direct_regs(mk, mw, g->spec).staged * threads && wpc % 4 == 0 && x.kred % 4 == 0;
     if (alt) wr = cdiv(w0, 4 * threads) * 4 * threads;  // whole rows of 16-byte quads
     const bool rows = 4 * (cdiv(wr, 4) * 4 + xr) <= kMaxLdsBytes;
     const int64_t wt = rows ? wr : w0, bytes = 4 * (cdiv(wt, 4) * 4 + (rows ? xr : x0));
