@@ -203,7 +203,10 @@ static int64_t direct_lds_layout(const OpX& x, const ct_schedule& s, int64_t thr
   };
   for (;;) {
     const bool padded = g->spec != SPEC_GENERIC;
-    const int step = mw * o.stride_w, xa = step % 4 == 0 ? 4 : (step % 2 == 0 ? 2 : 1);
+    // (1x1 stride-2 windows are read word by word: rows padded to 8 or 16 words put the rows
+    // of a tile 4 columns wide into the same banks, twice as slow)
+    const int step = mw * o.stride_w;
+    const int xa = g->spec == SPEC_1X1_S2 ? 1 : (step % 4 == 0 ? 4 : (step % 2 == 0 ? 2 : 1));
     const int64_t pitch = padded ? cdiv(g->iw_t, xa) * xa : g->iw_t;
     const int64_t wpc = (int64_t)ct * o.r * o.s;  // filter words of an output channel
     const int wa = mk > 1 || wpc % 4 == 0 ? 4 : 1;

@@ -62,6 +62,8 @@ static int check(const OpX& x, const ct_schedule& s, const Geom& g, int* ways) {
     if (!(sc == 1 && stc == 2)) {
       const int step = mw * stc, align = step % 4 == 0 ? 4 : (step % 2 == 0 ? 2 : 1);
       CHECK(g.d_pitch % align == 0);
+    } else {
+      CHECK(g.d_pitch == g.iw_t);  // read word by word: padded rows would only share banks
     }
   }
   return 0;
