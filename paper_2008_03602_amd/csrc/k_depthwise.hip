@@ -76,13 +76,13 @@ __device__ __forceinline__ DwThread dw_thread(const DwArgs& a) {
 // 160 sampled schedules each, against divisions, 64-bit addresses and strided rows: 30.5
 // to 18.7 us on the whole GPU, 102 to 56 us on a quarter.
 // WIDE: a block whose planes span more than 32-bit part offsets reach (geom_depthwise);
-// only the generic filter path has that variant.
+// with LDS only the generic filter path has that variant.
 template <int VEC, int RPT, bool LDS, int SPEC, bool WIDE>
 __global__ void __launch_bounds__(dw_max_threads(VEC * RPT))
 depthwise_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, float* __restrict__ y,
                      DwArgs a) {
   constexpr int RC = dw_spec_r(SPEC), STC = dw_spec_stride(SPEC);
-  static_assert(!WIDE || RC == 0, "the fixed filters have no wide variant");
+  static_assert(!WIDE || !LDS || RC == 0, "the fixed filters have no wide variant with LDS");
   const int R = RC ? RC : a.R, S = RC ? RC : a.S;
   const int sh = STC ? STC : a.sh, sw = STC ? STC : a.sw;
   const int dh = RC ? 1 : a.dh, dw = RC ? 1 : a.dw;
@@ -105,7 +105,10 @@ depthwise_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, f
   const unsigned wofs = part(live, (unsigned)td.ci * R * S);
 
   float wv[RC ? RC * RC : 1];
-  if constexpr (RC != 0) {
+  if constexpr (WIDE && RC != 0) {
+#pragma unroll
+    for (int i = 0; i < RC * RC; ++i) wv[i] = load_or_zero(w, (int64_t)c * RC * RC + i, live);
+  } else if constexpr (RC != 0) {
 #pragma unroll
     for (int r = 0; r < RC; ++r) bload3(rwt, wofs + r * 12u, wv + r * 3);
   }
@@ -166,7 +169,29 @@ depthwise_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, f
   const float* xs = smem + (td.ni * a.tc + td.ci) * plane + td.rowg * RPT * sh * a.iw_t + td.colg * sw;
   const unsigned pofs = part(live, ((unsigned)td.ni * C + td.ci) * HW);
   const int ih0 = oh * sh - ph;
-  if constexpr (RC != 0) {
+  if constexpr (WIDE && !LDS) {
+    // one output row at a time: planes this large come from HBM, and the rows of a tap are
+    // far apart
+    const float* xc = x + ((int64_t)(live ? n : 0) * C + (live ? c : 0)) * HW;
+#pragma unroll
+    for (int u = 0; u < RPT; ++u) {
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const int gh = ih0 + u * sh + r * dh;
+        const bool hok = live && (unsigned)gh < (unsigned)H;
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+          const float wt = RC ? wv[r * RC + s] : (live ? w[((int64_t)c * R + r) * S + s] : 0.f);
+#pragma unroll
+          for (int v = 0; v < VEC; ++v) {
+            const int gw = (bk.ow0 + td.colg + v * a.cols) * sw - pw + s * dw;
+            const float xv = load_or_zero(xc, (int64_t)gh * W + gw, hok && (unsigned)gw < (unsigned)W);
+            acc[u][v] = fmaf(wt, xv, acc[u][v]);
+          }
+        }
+      }
+    }
+  } else if constexpr (RC != 0) {
     constexpr int NIN = (RPT - 1) * STC + RC;  // input rows of the thread's outputs
     unsigned cofs[VEC][RC];
     if constexpr (!LDS) {
@@ -208,7 +233,6 @@ depthwise_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, f
       }
     }
   } else {
-    const float* xc = x + ((int64_t)(live ? n : 0) * C + (live ? c : 0)) * HW;
     for (int r = 0; r < R; ++r) {
       for (int s = 0; s < S; ++s) {
         float wt;
@@ -227,8 +251,6 @@ depthwise_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, f
             float xv;
             if constexpr (LDS)
               xv = xs[(u * sh + r * dh) * a.iw_t + v * a.cols * sw + s * dw];
-            else if constexpr (WIDE)
-              xv = load_or_zero(xc, (int64_t)gh * W + gw, live && hok && (unsigned)gw < (unsigned)W);
             else
               xv = bload1(rx, rofs + part((unsigned)gw < (unsigned)W, gw));
             acc[u][v] = fmaf(wt, xv, acc[u][v]);
@@ -366,7 +388,11 @@ static DwFn dw_q4_pick(int rpt) {
 
 template <int VEC, int RPT, bool LDS>
 static DwFn dw_pick_spec(int spec, bool wide) {
-  if (wide) return depthwise_f32_kernel<VEC, RPT, LDS, 0, true>;
+  if (wide) {
+    if (!LDS && spec == SPEC_3X3_S1) return depthwise_f32_kernel<VEC, RPT, LDS, LDS ? 0 : 3, true>;
+    if (!LDS && spec == SPEC_3X3_S2) return depthwise_f32_kernel<VEC, RPT, LDS, LDS ? 0 : 4, true>;
+    return depthwise_f32_kernel<VEC, RPT, LDS, 0, true>;
+  }
   switch (spec) {
     case SPEC_3X3_S1: return depthwise_f32_kernel<VEC, RPT, LDS, 3, false>;
     case SPEC_3X3_S2: return depthwise_f32_kernel<VEC, RPT, LDS, 4, false>;

@@ -314,8 +314,8 @@ static int geom_depthwise(const OpX& x, const ct_schedule& s, Geom* g, std::stri
   g->tiles_c = cdiv(o.c, tc);
   g->tiles_n = cdiv(o.n, nb);
   // a block's planes, rows and columns are addressed by 32-bit part offsets where they
-  // (and the staging counters' run past them) stay in that range; else the wide variant
-  const int64_t span = ((int64_t)nb * o.c + tc) * std::max((int64_t)o.h * o.w, x.oh * x.ow);
+  // stay in that range; else the wide variant
+  const int64_t span = ((int64_t)(nb - 1) * o.c + tc) * std::max((int64_t)o.h * o.w, x.oh * x.ow);
   g->dw_wide = !s.knob[Q4] && (4 * span >= kPartOob || 4 * (int64_t)tc * o.r * o.s >= kPartOob);
   g->threads = (int)threads;
   g->lds_bytes = (int)lbytes;
@@ -657,7 +657,7 @@ int ct_kernel_name(const ct_op* op, const ct_schedule* s, char* buf, int cap) {
                     tf(g.d_alt));
       break;
     case CT_FAM_DEPTHWISE_F32: {
-      const int spec = !g.dw_wide && (g.spec == SPEC_3X3_S1 || g.spec == SPEC_3X3_S2) ? g.spec : 0;
+      const int spec = !(g.dw_wide && k[dw_knob::LDS]) && (g.spec == SPEC_3X3_S1 || g.spec == SPEC_3X3_S2) ? g.spec : 0;
       if (k[dw_knob::Q4])
         std::snprintf(tmp, sizeof tmp, "depthwise_q4_kernel<%d, %d>", spec == SPEC_3X3_S2 ? 2 : 1, k[dw_knob::RPT]);
       else

@@ -109,29 +109,39 @@ def test_direct_tiles_whose_padded_layout_exceeds_the_lds_run_generic():
         check_close(op, yd.cpu().numpy(), ref, a, sched_str(s), split=4)
 
 
-def test_depthwise_planes_beyond_the_32_bit_part_offsets():
-    # two planes of 512 MB + : a block's planes span more than 2^30 bytes
-    op = _dw("huge", 1, 2, 8200, 16400, 3, 3, 1, (1, 1))
+# two planes of 512 MB and more (a block's planes span more than 2^30 bytes) with each filter
+# path, and 128 planes of 8 MB, of which a block's 16 do not
+@pytest.mark.parametrize("op,tc,wide", [
+    (_dw("huge", 1, 2, 8200, 16400, 3, 3, 1, (1, 1)), 2, True),
+    (_dw("huge_s2", 1, 2, 8200, 16400, 3, 3, 2, (1, 1)), 2, True),
+    (_dw("huge_5x3", 1, 2, 8200, 16400, 5, 3, 1, (2, 1)), 2, True),
+    (_dw("hd", 1, 128, 1088, 1920, 3, 3, 1, (1, 1)), 16, False),
+], ids=lambda v: getattr(v, "name", None))
+def test_depthwise_planes_around_the_32_bit_part_offsets(op, tc, wide):
     gen = torch.Generator(device="cuda")
     gen.manual_seed(7)
     xd = torch.rand(op.x_shape(), generator=gen, device="cuda") * 2 - 1
     wd = torch.rand(op.w_shape(), generator=gen, device="cuda") * 2 - 1
     ref = torch.zeros(op.y_shape(), device="cuda")
-    p = torch.nn.functional.pad(xd, (1, 1, 1, 1))
-    for r in range(3):
-        for s in range(3):
-            ref += p[:, :, r:r + op.h, s:s + op.w] * wd[:, :, r, s].reshape(1, -1, 1, 1)
+    p = torch.nn.functional.pad(xd, (op.pad_w, op.pad_w, op.pad_h, op.pad_h))
+    st = op.stride_h
+    for r in range(op.r):
+        for s in range(op.s):
+            part = p[:, :, r:r + (op.oh - 1) * st + 1:st, s:s + (op.ow - 1) * st + 1:st]
+            ref += part * wd[:, :, r, s].reshape(1, -1, 1, 1)
     del p
     yd = torch.empty(op.y_shape(), device="cuda")
+    n = op.r * op.s
     for lds in (0, 1):
-        s = L.make_schedule(W.FAM_DEPTHWISE_F32, (2, 8, 64, 2, 2, lds, 1, 0, 0))
+        s = L.make_schedule(W.FAM_DEPTHWISE_F32, (tc, 8, 64 if tc == 2 else 16, 2, 2, lds, 1, 0, 0))
         assert L.ct_validate(op, s) == L.S_OK
-        note("huge " + sched_str(s))
+        assert L.ct_kernel_name(op, s).endswith("true>" if wide else "false>")
+        note(op.name + " " + sched_str(s))
         yd.fill_(float("nan"))
         torch.cuda.synchronize()
         L.conv2d_run(op, s, xd, wd, yd)
-        # 9 products of at most 1: both sums err by at most 9 roundings of at most 9 * 2^-24
-        assert float((yd - ref).abs().max()) <= 2 * 9 * 9 * 2.0 ** -24
+        # n products of at most 1: both sums err by at most n roundings of at most n * 2^-24
+        assert float((yd - ref).abs().max()) <= 2 * n * n * 2.0 ** -24
 
 
 def _pw(name, n, c, h, w, k, stride=1):

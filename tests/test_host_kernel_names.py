@@ -53,6 +53,15 @@ def test_wide_depthwise_blocks_are_named_as_such(kernels):
     assert L.ct_kernel_name(wide, s).endswith(", true>")
     small = _f32("small", 2, 64, 2, 3, 3, 1, 1, groups=2, w=64)
     assert L.ct_kernel_name(small, s) == "depthwise_f32_kernel<2, 2, false, 3, false>"
+    # fixed filters keep their path without LDS
+    assert L.ct_kernel_name(wide, s) == "depthwise_f32_kernel<2, 2, false, 3, true>"
+    # what counts is what one block reaches: here 16 planes of 8 MB of an image of 1 GB, or
+    # the same channels of two images
+    hd = _f32("hd", 128, 1088, 128, 3, 3, 1, 1, groups=128, n=2, w=1920)
+    for nb, ending in ((1, "false>"), (2, "true>")):
+        t = L.make_schedule(W.FAM_DEPTHWISE_F32, (16, 8, 16, 2, 2, 0, nb, 0, 0))
+        assert L.ct_validate(hd, t) == L.S_OK
+        assert L.ct_kernel_name(hd, t).endswith(ending)
     # the kernel of 4 consecutive columns addresses planes of any size
     q4 = L.make_schedule(W.FAM_DEPTHWISE_F32, (2, 8, 64, 4, 2, 0, 1, 0, 1))
     assert L.ct_kernel_name(wide, q4) == "depthwise_q4_kernel<1, 2>"
