@@ -27,6 +27,10 @@
 //     tiles wait once. Rows lie unpadded; the 16-byte groups of a row are
 //     permuted by the low bits of its number, so that the 16 rows a fragment
 //     reads at one k lie in distinct banks.
+//     The copies take 16-byte addresses; a tensor off them goes through
+//     registers, eight loads of a lane at a time (D = 1). Read without LDS
+//     instead, every fragment row at its own misaligned addresses, a
+//     1024-channel layer's schedules took up to 4 times as long.
 //   * Reads are range-checked buffer loads from a base that advances with k:
 //     no bounds branch, no select, no address arithmetic per load.
 // Measured, 3076 sampled schedules of the MobileNet-v2 b16 pointwise layers and
@@ -173,7 +177,7 @@ igemm_bf16_kernel(const unsigned short* __restrict__ x, const unsigned short* __
     for (int u = 0; u < D; ++u)
       if (st + u < n) mma(u);
   } else {
-    extern __shared__ unsigned short lds16[];
+    extern __shared__ __align__(16) unsigned short lds16[];
     constexpr int VPR = KC / 8, RPC = 64 / VPR;  // 16-byte groups of a row, rows of a wave's copy
     constexpr int SW = VPR == 4 ? 2 : VPR == 8 ? 1 : 0;
     const int nw_shift = 31 - __builtin_clz(a.threads >> 6), qa = a.bm / RPC, q_end = (a.bm + a.bn) / RPC;
@@ -205,17 +209,27 @@ igemm_bf16_kernel(const unsigned short* __restrict__ x, const unsigned short* __
       int cq = nq, ca = na;
       asm volatile("" : "+s"(cq), "+s"(ca));
       auto copies = [&](auto tail) __attribute__((always_inline)) {
+        constexpr int G = D ? 8 : 4;
 #pragma unroll
-        for (int i0 = 0; i0 < 2 * kMaxLoadsPerThread; i0 += 4)
+        for (int i0 = 0; i0 < 2 * kMaxLoadsPerThread; i0 += G)
           if (i0 < cq) {
+            bf16x8 v[D ? G : 1];
 #pragma unroll
-            for (int i = i0; i < i0 + 4; ++i)
+            for (int i = i0; i < i0 + G; ++i)
               if (i < cq) {
                 const int q = wave + (i << nw_shift);
                 unsigned o = off[i];
                 if constexpr (tail.value) o = k + 8 * col(q) < a.C ? o : kOobBytes;
-                copy16_to_lds(i < ca ? rx : rw, (float*)(dst + q * 512), o);
+                if constexpr (D)
+                  v[i - i0] = load8(i < ca ? rx : rw, o);
+                else
+                  copy16_to_lds(i < ca ? rx : rw, (float*)(dst + q * 512), o);
               }
+            if constexpr (D) {
+#pragma unroll
+              for (int i = i0; i < i0 + G; ++i)
+                if (i < cq) *(bf16x8*)(dst + (wave + (i << nw_shift)) * 512 + 8 * lane) = v[i - i0];
+            }
           }
       };
       if (k + KC <= a.C)
@@ -304,9 +318,9 @@ static IgBf16Fn bf_pick_kc(int kc, int ring) {
     return nullptr;  // accumulator tiles the validator rejects: not instantiated
   } else {
     switch (kc) {
-      case 32: return igemm_bf16_kernel<MF, TM, TN, 32, 0>;
-      case 64: return igemm_bf16_kernel<MF, TM, TN, 64, 0>;
-      case 128: return igemm_bf16_kernel<MF, TM, TN, 128, 0>;
+      case 32: return ring ? igemm_bf16_kernel<MF, TM, TN, 32, 1> : igemm_bf16_kernel<MF, TM, TN, 32, 0>;
+      case 64: return ring ? igemm_bf16_kernel<MF, TM, TN, 64, 1> : igemm_bf16_kernel<MF, TM, TN, 64, 0>;
+      case 128: return ring ? igemm_bf16_kernel<MF, TM, TN, 128, 1> : igemm_bf16_kernel<MF, TM, TN, 128, 0>;
     }
     constexpr int most = bf16_most_steps(TM + TN);
     if (ring == 1) return igemm_bf16_kernel<MF, TM, TN, 0, 1>;
@@ -348,11 +362,11 @@ int launch_igemm_bf16(const OpX& x, const ct_schedule& s, const Geom& g, const v
   a.dtn = make_fastdiv(g.tiles_k); a.dohw = make_fastdiv(x.oh * x.ow); a.dow = make_fastdiv(x.ow);
   a.tiles_m = (int)g.tiles_h; a.tiles_n = (int)g.tiles_k; a.swz = s.knob[SWZ];
   a.ny = x.ny;
-  // copies into LDS take 16 bytes at 16-byte addresses; tensors off them are
-  // read without LDS, in the same order
+  // copies into LDS take 16 bytes at 16-byte addresses; tensors off them go
+  // through registers
   const bool aligned = ((uintptr_t)xin | (uintptr_t)w) % 16 == 0;
-  const int kc = s.knob[LDS] && aligned ? s.knob[KC] : 0;
-  const int ring = s.knob[LDS] ? bf16_most_steps(s.knob[TM] + s.knob[TN]) : g.bf_ring;
+  const int kc = s.knob[LDS] ? s.knob[KC] : 0;
+  const int ring = s.knob[LDS] ? !aligned : g.bf_ring;
   IgBf16Fn fn = s.knob[MF] == 32 ? bf_pick_tm<32>(s.knob[TM], s.knob[TN], kc, ring)
                                  : bf_pick_tm<16>(s.knob[TM], s.knob[TN], kc, ring);
   if (!fn) {
@@ -361,7 +375,7 @@ int launch_igemm_bf16(const OpX& x, const ct_schedule& s, const Geom& g, const v
   }
   dim3 grid((unsigned)(g.tiles_h * g.tiles_k), (unsigned)g.split);
   float* out = g.split > 1 ? ws : (float*)y;
-  hipLaunchKernelGGL(fn, grid, dim3(g.threads), kc ? g.lds_bytes : 0, (hipStream_t)stream,
+  hipLaunchKernelGGL(fn, grid, dim3(g.threads), g.lds_bytes, (hipStream_t)stream,
                      (const unsigned short*)xin, (const unsigned short*)w, out, a);
   if (hipGetLastError() != hipSuccess) return -1;
   if (g.split > 1) return launch_split_reduce(ws, (float*)y, x.ny, g.split, stream);
