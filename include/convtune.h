@@ -95,19 +95,27 @@ typedef struct ct_op {
  * encodings of the grid (the validator decides which run on an op).
  *   CT_FAM_DIRECT_F32: toh, tow (output tile), tk (output channels per
  *     block), mk, mw (channels and columns per thread), lds (stage halo and
- *     filter in LDS), ct (channels per chunk), split (reduction split),
- *     unroll (channels unrolled together).
+ *     filter in LDS), ct (channels per chunk; without LDS only the bounds of
+ *     split ranges), split (reduction split), unroll (filters without a path
+ *     of their own, which are those other than 1x1, 3x3 pad 1 and 5 or 7
+ *     columns at column stride 1 or 2 and no column dilation, and tiles whose
+ *     padded layout exceeds the LDS: channels unrolled together, or from LDS
+ *     with rows of four taps and more, taps read together by twos or fours).
  *   CT_FAM_DEPTHWISE_F32: tc (channels per block), toh, tow, vec, rpt
  *     (columns and rows per thread), lds, nb (images per block), order
  *     (block numbering: tiles fastest or channel groups fastest), q4 (4
  *     consecutive columns per thread from 16-byte row loads).
  *   CT_FAM_IGEMM_BF16: mfma (16 or 32: the MFMA tile), tm, tn (MFMA tiles
- *     per wave), wm, wn (waves per block), kc (input channels per chunk),
- *     lds (stage operands in LDS), split, swizzle (XCD-band block order).
+ *     per wave), wm, wn (waves per block), kc (input channels per chunk;
+ *     without LDS only the bounds of split ranges), lds (stage operands in
+ *     LDS), split, swizzle (XCD-band block order).
  *   CT_FAM_IGEMM_F32: mfma, tm, tn, wm, wn, ws (reduction groups per
  *     block), tpw (pixel tile width), cpc (channels per chunk), stages (1:
  *     one LDS stage; 2: two; 3: two, with four loader waves issuing every
- *     copy), split. */
+ *     copy), split.
+ * Where a knob says that it does not apply, schedules that differ only in it
+ * run the same program. All of them validate and a sample may hold several;
+ * guided search turns to new programs first. */
 typedef struct ct_schedule {
     int32_t family;
     int32_t knob[CT_MAX_KNOBS];
@@ -439,7 +447,10 @@ typedef struct ct_search_result {
  * so->explore of it (all of it when nothing has been measured OK yet) drawn
  * at random: the applicable kernel families in turn, uniformly within each,
  * so a small family is explored as much as a large one. Random draws that hit
- * measured schedules are redrawn. Writes min(cap, so->batch) distinct valid
+ * measured schedules are redrawn. Schedules that run the same program count
+ * as one: a batch holds new programs, except one schedule of a measured
+ * program where the model expects more of it than of any new one, and except
+ * where no new program is left. Writes min(cap, so->batch) distinct valid
  * schedules not among `measured` (fewer once the space runs out) to out,
  * count in *n_out. Same inputs and round give the same output. */
 int ct_search_propose(const ct_op *op, const ct_schedule *measured, const float *lat_us, const int32_t *status,

@@ -149,6 +149,10 @@ struct Geom {
 // Validates s on x and fills g. Returns CT_OK or CT_S_INVALID (reason in why).
 int compute_geom(const OpX& x, const ct_schedule& s, Geom* g, std::string* why);
 
+// s with the knobs that its kernel and launch do not depend on at their first values: two
+// valid schedules of an op with the same one run the same program. g: compute_geom's.
+ct_schedule program_of(const ct_schedule& s, const Geom& g);
+
 // ---- kernel launchers (one per family, in the .hip files) ----
 // Return 0, -1 on a HIP launch error, or -2 when the arguments are refused
 // (reason given to set_error).

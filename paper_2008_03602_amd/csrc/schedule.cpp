@@ -340,8 +340,10 @@ static int geom_igemm_bf16(const OpX& x, const ct_schedule& s, Geom* g, std::str
   const int threads = 64 * wm * wn;
   if (threads > mfma_thread_limit(acc_regs)) REJECT("too many threads for the accumulator tile");
   if (!lds) {
+    // a bound of the space, not of registers: the ring's depth does not depend on kc
+    // (bf16_most_steps), which only bounds split ranges here
     const int steps = kc / (mf == 32 ? 16 : 32);
-    if (steps > 4 || steps * (tm + tn) > 16) REJECT("too many fragments held in registers");
+    if (steps > 4 || steps * (tm + tn) > 16) REJECT("chunk too long without LDS");
   }
   // the epilogue's buffer stores address a wave tile of y in 32-bit bytes
   if (4 * x.ny >= ((int64_t)1 << 31)) REJECT("output too large for 32-bit buffer offsets");
@@ -530,6 +532,23 @@ int compute_geom(const OpX& x, const ct_schedule& s, Geom* g, std::string* why) 
   g->kernels = g->split > 1 ? 2 : 1;
   g->ws_floats = g->split > 1 ? (int64_t)g->split * x.ny : 0;
   return CT_OK;
+}
+
+ct_schedule program_of(const ct_schedule& s, const Geom& g) {
+  ct_schedule p = s;
+  auto first = [&](int knob) { p.knob[knob] = family_def(s.family)->knobs[knob].vals[0]; };
+  if (s.family == CT_FAM_DIRECT_F32) {
+    using namespace direct_knob;
+    // the paths of a filter of their own have no unroll variant; nor has the one for long
+    // filter rows where the registers end (k_direct.inc.h)
+    const bool rows8 = s.knob[LDS] && g.d_alt && s.knob[MK] == 8 && s.knob[MW] == 1;
+    if (g.spec != SPEC_GENERIC || rows8) first(UNR);
+    if (!s.knob[LDS] && s.knob[SPLIT] == 1) first(CT);  // registers only: no chunks
+  } else if (s.family == CT_FAM_IGEMM_BF16) {
+    using namespace bf16_knob;
+    if (!s.knob[LDS] && s.knob[SPLIT] == 1) first(KC);
+  }
+  return p;
 }
 
 uint64_t splitmix64_next(uint64_t* state) {

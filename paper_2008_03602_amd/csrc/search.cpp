@@ -59,6 +59,13 @@ uint64_t key_of(const ct_schedule& s) {
   return (uint64_t)s.family << 48 | idx;
 }
 
+// Key of the program that a schedule of x runs: schedules that differ only in knobs their
+// kernel does not depend on share it.
+uint64_t program_key(const OpX& x, const ct_schedule& s) {
+  Geom g;
+  return key_of(compute_geom(x, s, &g, nullptr) == CT_OK ? program_of(s, g) : s);
+}
+
 int build_space(const ct_op& op, Space* sp) {
   std::string why;
   if (!derive_op(op, &sp->x, &why)) { set_error(why); return CT_E_ARG; }
@@ -265,12 +272,24 @@ const ct_schedule& draw(const Space& sp, uint64_t draw_no, uint64_t* st) {
 
 int propose(const Space& sp, const ct_schedule* meas, const float* lat, const int32_t* st, int n,
             const ct_search_opts& so, int round, ct_schedule* out, int want) {
-  std::unordered_set<uint64_t> seen;
-  for (int i = 0; i < n; ++i) seen.insert(key_of(meas[i]));
+  // Schedules that share a program are one measurement: a batch holds programs not yet
+  // measured, each by its best predicted schedule. Every schedule stays reachable: one of a
+  // measured program is proposed where the model expects more of it than of any new program
+  // (one a batch), and where no new program is left.
+  std::unordered_set<uint64_t> seen, seen_programs;
+  for (int i = 0; i < n; ++i) {
+    seen.insert(key_of(meas[i]));
+    seen_programs.insert(program_key(sp.x, meas[i]));
+  }
   uint64_t rng = so.seed ^ 0x5A17E5EA5C4ull ^ (0x9E3779B97F4A7C15ull * (uint64_t)(round + 1));
   splitmix64_next(&rng);
   std::vector<std::pair<double, uint64_t>> picked;  // (predicted, key), in selection order
-  std::unordered_set<uint64_t> chosen;
+  std::unordered_set<uint64_t> chosen, chosen_programs;
+  auto pick = [&](double predicted, uint64_t key, uint64_t program) {
+    picked.emplace_back(predicted, key);
+    chosen.insert(key);
+    chosen_programs.insert(program);
+  };
 
   Model model;
   const int cus = so.cus > 0 ? so.cus : 256;
@@ -292,7 +311,8 @@ int propose(const Space& sp, const ct_schedule* meas, const float* lat, const in
     }
     for (auto& v : ok)
       std::sort(v.begin(), v.end(), [&](int a, int b) { return lat[a] < lat[b] || (lat[a] == lat[b] && a < b); });
-    std::unordered_map<uint64_t, double> pool;
+    std::unordered_map<uint64_t, std::pair<double, uint64_t>> pool;  // program -> (predicted, key)
+    std::pair<double, uint64_t> again(INFINITY, 0);                   // best of a measured program
     std::vector<double> feat;
     const int chains = std::max(1, so.sa_chains);
     const int steps = std::max(1, so.sa_steps);
@@ -309,18 +329,25 @@ int propose(const Space& sp, const ct_schedule* meas, const float* lat, const in
           s = c2;
           e = e2;
         }
-        const uint64_t k = key_of(s);
-        if (!seen.count(k)) pool.emplace(k, e);
+        const std::pair<double, uint64_t> pk(e, key_of(s));
+        if (seen.count(pk.second)) continue;
+        const uint64_t program = program_key(sp.x, s);
+        if (seen_programs.count(program)) {
+          again = std::min(again, pk);
+        } else {
+          auto& best_of = pool.emplace(program, pk).first->second;
+          best_of = std::min(best_of, pk);
+        }
       }
     }
-    std::vector<std::pair<double, uint64_t>> ranked;
+    std::vector<std::pair<std::pair<double, uint64_t>, uint64_t>> ranked;
     ranked.reserve(pool.size());
     for (const auto& kv : pool) ranked.emplace_back(kv.second, kv.first);
     std::sort(ranked.begin(), ranked.end());
-    for (const auto& pk : ranked) {
+    if (again.first < (ranked.empty() ? INFINITY : ranked[0].first.first)) pick(again.first, again.second, again.second);
+    for (const auto& r : ranked) {
       if ((int)picked.size() >= n_model) break;
-      picked.push_back(pk);
-      chosen.insert(pk.second);
+      pick(r.first.first, r.first.second, r.second);
     }
   }
   // exploration: uniform draws over the unmeasured space, families in turn
@@ -330,18 +357,20 @@ int propose(const Space& sp, const ct_schedule* meas, const float* lat, const in
   while ((int)picked.size() < want && guard < 64 * want) {
     const ct_schedule& s = draw(sp, turn0 + (uint64_t)guard, &rng);
     ++guard;
-    const uint64_t k = key_of(s);
-    if (seen.count(k) || chosen.count(k)) continue;
-    picked.emplace_back(NAN, k);
-    chosen.insert(k);
+    const uint64_t program = program_key(sp.x, s);
+    if (seen_programs.count(program) || chosen_programs.count(program)) continue;
+    pick(NAN, key_of(s), program);
   }
-  if ((int)picked.size() < want) {  // nearly exhausted: scan from a random start
-    const uint64_t start = splitmix64_next(&rng) % size;
+  // nearly exhausted: scan from a random start, first for new programs
+  const uint64_t start = (int)picked.size() < want ? splitmix64_next(&rng) % size : 0;
+  for (int pass = 0; pass < 2; ++pass) {
     for (uint64_t i = 0; i < size && (int)picked.size() < want; ++i) {
-      const uint64_t k = key_of(sp.all[(start + i) % size]);
+      const ct_schedule& s = sp.all[(start + i) % size];
+      const uint64_t k = key_of(s);
       if (seen.count(k) || chosen.count(k)) continue;
-      picked.emplace_back(NAN, k);
-      chosen.insert(k);
+      const uint64_t program = program_key(sp.x, s);
+      if (pass == 0 && (seen_programs.count(program) || chosen_programs.count(program))) continue;
+      pick(NAN, k, program);
     }
   }
   int m = 0;

@@ -137,3 +137,40 @@ def test_small_space_runs_out_cleanly():
         meas += p
     assert len(meas) == n_space
     assert len({_key(s) for s in meas}) == n_space
+
+
+def _program(op, s):
+    """The schedule with the knobs that its kernel does not depend on left out: unroll where
+    the kernel's name does not tell the two values apart, and the chunk length of schedules
+    that read without LDS and without a split."""
+    k = list(s.knob)
+    lds, split, length, unroll = {1: (5, 7, 6, 8), 3: (6, 7, 5, None)}.get(s.family, (None,) * 4)
+    if unroll is not None:
+        if len({L.ct_kernel_name(op, L.make_schedule(s.family, k[:unroll] + [u])) for u in (1, 2)}) == 1:
+            k[unroll] = 0
+    if lds is not None and not k[lds] and k[split] == 1:
+        k[length] = 0
+    return (s.family,) + tuple(k)
+
+
+@pytest.mark.parametrize("op", [OP, W.resnet18()[11], W.conv("f9", 1, 8, 40, 16, 9, 1, 4),
+                                W.mobilenet_v2_pointwise(16)[4]], ids=lambda o: o.name)
+def test_a_batch_holds_new_programs(op):
+    # schedules that differ only in a knob their kernel does not depend on run the same
+    # program; all but one of a batch are programs not measured before
+    rng = np.random.default_rng(3)
+    tab, meas, lat = {}, [], []
+
+    def f(s):
+        return float(np.exp(sum(tab.setdefault((s.family, i, v), rng.uniform(0.0, 1.0))
+                                for i, v in enumerate(_program(op, s)[1:]))))
+
+    so = L.make_search_opts(seed=2, batch=16)
+    programs = set()
+    for r in range(8):
+        batch = L.ct_search_propose(op, meas, np.array(lat, np.float32), np.zeros(len(lat), np.int32), so, r)
+        new = {_program(op, s) for s in batch} - programs
+        assert len(batch) == 16 and len(new) >= 15
+        programs |= new
+        meas += batch
+        lat += [f(s) for s in batch]
