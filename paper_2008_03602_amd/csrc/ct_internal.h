@@ -97,11 +97,12 @@ constexpr int direct_max_threads(int tile) { return tile >= 16 ? 512 : 1024; }
 // filter. `ring` units stay in flight, so that the LDS latency of a unit passes behind the
 // multiply-adds of those before it: 2 where a unit's multiply-adds take longer than the
 // latency, up to 4 where they are short, fewer where the registers end. `staged`: words
-// per thread that a chunk may have to go through registers.
+// per thread that a chunk may have to go through registers. `plan`: copies of the filter,
+// and of the halo, whose offsets a deep chunk's variant keeps.
 struct DirectRegs {
   int limit;           // registers per thread
   int x_words, w_words;  // operand words of a unit
-  int ring, staged;
+  int ring, staged, plan;
 };
 constexpr DirectRegs direct_regs(int mk, int mw, int spec) {
   const int sc = direct_spec_s(spec), stc = direct_spec_stride(spec);
@@ -113,8 +114,10 @@ constexpr DirectRegs direct_regs(int mk, int mw, int spec) {
   const int fit = (r.limit - mk * mw - 72) / unit;
   const int want = clocks >= 160 ? 2 : (clocks >= 48 || sc == 1 ? 3 : 4);
   r.ring = fit < 1 ? 1 : (fit < want ? fit : want);
-  const int words = (r.limit - mk * mw - (sc ? r.ring * unit : 24) - (sc == 1 ? 60 : 44)) / 2;
+  const int left = r.limit - mk * mw - (sc ? r.ring * unit : 24);
+  const int words = (left - (sc == 1 ? 60 : 44)) / 2, copies = (left - 56) / 2;
   r.staged = words >= 24 && r.limit == 256 ? 24 : (words >= 16 ? 16 : (words >= 12 ? 12 : (words >= 8 ? 8 : 6)));
+  r.plan = copies < 4 ? 4 : (copies < 12 ? copies : 12);
   return r;
 }
 

@@ -416,8 +416,7 @@ direct_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, floa
     // copies then take no vector instruction but themselves (lanes past a
     // region's end write zeros into its padding). kPlan is what fits beside the
     // accumulators and the units in flight, so that nothing goes to scratch.
-    constexpr int kRoom = (kLimit - MK * MW - (SC ? D * (NW + WW) : 24) - 56) / 2;
-    constexpr int kPlan = !DEEP ? 1 : (kRoom < 4 ? 4 : (kRoom < 12 ? kRoom : 12));
+    constexpr int kPlan = DEEP ? kHeld.plan : 1;
     unsigned pw[kPlan], px[kPlan];
     int npw = 0, npx = 0;
     const int gq = a.ks / 4, ng = min(a.tk / MK, (K - k0 + MK - 1) / MK);

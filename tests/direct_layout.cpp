@@ -2,7 +2,8 @@
 // of the ops listed in the input file (one per line, the 16 numbers of ct_op), the words
 // that the kernel's copies write and its windows read lie inside the block's LDS, wide
 // reads are aligned, and a chunk goes the way the instance's registers allow. Prints one
-// line per op and "done"; any fault ends the run with status 1.
+// line per op and "done"; any fault ends the run with status 1. With a second argument
+// also how each schedule's chunks go, in the words of direct_paths.py.
 #include <cstdint>
 #include <cstdio>
 #include <vector>
@@ -69,6 +70,28 @@ static int check(const OpX& x, const ct_schedule& s, const Geom& g, int* ways) {
   return 0;
 }
 
+static void list(const ct_schedule& s, const Geom& g) {
+  using namespace direct_knob;
+  const int mk = s.knob[MK], threads = g.threads, groups = s.knob[TK] / mk;
+  const DirectRegs held = direct_regs(mk, s.knob[MW], g.spec);
+  auto rows = [&](int64_t words) { return (int)cdiv(words, threads); };
+  auto fills = [&](int words) { return 2 * words > rows(words) * threads; };
+  const int plane = g.ih_t * g.d_pitch, quads = g.d_ks / 4;
+  const int64_t xt = (int64_t)s.knob[CT] * plane;
+  const int nst = rows(g.d_wt) + rows(xt);
+  for (int i = 0; i < COUNT; ++i) std::printf("%d ", s.knob[i]);
+  if (g.spec != SPEC_GENERIC && g.d_alt) {
+    if (rows((int64_t)groups * quads) <= held.plan && rows(xt) <= held.plan)
+      std::printf("plan\n");
+    else
+      std::printf("deep %d %d %d\n", fills(plane), fills(quads), fills(g.d_ks));
+  } else if (nst <= held.staged) {
+    std::printf("staged %d\n", nst);
+  } else {
+    std::printf("copied %d %d\n", fills(plane), fills(g.d_ks));
+  }
+}
+
 int main(int argc, char** argv) {
   std::FILE* f = argc > 1 ? std::fopen(argv[1], "r") : nullptr;
   if (!f) return 2;
@@ -89,6 +112,7 @@ int main(int argc, char** argv) {
       if (!s.knob[direct_knob::LDS] || compute_geom(x, s, &g, nullptr) != CT_OK) continue;
       ++n;
       if (check(x, s, g, ways)) return 1;
+      if (argc > 2) list(s, g);
     }
     std::printf("op %d: %d schedules, %d through registers, %d copied, %d with a plan\n", ops++, n, ways[0], ways[1],
                 ways[2]);

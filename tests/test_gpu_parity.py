@@ -11,6 +11,7 @@ import numpy as np
 import pytest
 import torch
 
+import direct_paths as DP
 from paper_2008_03602_amd import _lib as L, workloads as W
 from gpu_util import check_close, device_ready, make_inputs, note, reference, sched_str, to_device
 
@@ -182,73 +183,70 @@ def test_every_family_covered_on_config1_shape():
         check_close(op, yd.cpu().numpy(), ref, a, "config1 " + sched_str(s), split=4)
 
 
-def _fixed_filter(op):
-    """The 1x1 / 3x3 specialisations (stride 1 or 2, no dilation, 'same' padding)."""
-    sq = op.r == op.s and op.stride_h == op.stride_w and op.stride_h in (1, 2) and op.dil_h == op.dil_w == 1
-    return sq and ((op.r == 1 and op.pad_h == op.pad_w == 0) or (op.r == 3 and op.pad_h == op.pad_w == 1))
-
-
 def _direct_class(op, s):
-    """Which operand path a direct schedule takes (mirrors the kernel's choice)."""
-    toh, tow, tk, mk, mw, lds, ct, split, unr = (s.knob[i] for i in range(9))
-    cols = tow // mw
-    threads = (tk // mk) * toh * cols
-    if not lds:
-        kind = "regs-fixed" if _fixed_filter(op) else "regs"
-        return kind + ("-uniform-w" if (toh * cols) % 64 == 0 else "")
-    ih = (toh - 1) * op.stride_h + (op.r - 1) * op.dil_h + 1
-    iw = (tow - 1) * op.stride_w + (op.s - 1) * op.dil_w + 1
-    xt, wt = ct * ih * iw, tk * ct * op.r * op.s
-    n_stage = max(-(-xt // threads), -(-wt // threads))
-    tile = mk * mw
-    # deepest register prefetch the instance allows (launch bound 512 threads
-    # from 16 accumulators up, else 1024)
-    cap = 16 if tile >= 16 else (0 if unr == 2 and tile >= 8 else (4 if unr == 2 and tile >= 4 else 8))
-    if cap and n_stage <= cap:
-        return "prefetch-%d" % next(d for d in (2, 4, 8, 16) if n_stage <= d)
-    return "batch16" if n_stage >= 16 else "batch4"
+    """Which operand path a direct schedule takes: its kernel's specialisation and variant,
+    and with LDS the way its chunks go there (staged words by the lengths that have loops
+    of their own)."""
+    spec, alt = DP.kernel(op, s)
+    if not s.knob[DP.LDS]:
+        return "regs spec %d%s" % (spec, " scalar-w" if alt else "")
+    way = DP.lds_way(op, s)
+    if way[0] == "staged":
+        return "lds spec %d staged-%d" % (spec, next(n for n in (2, 4, 6, 8, 12, 16, 24) if way[1] <= n))
+    return "lds spec %d " % spec + " ".join(str(v) for v in way)
 
 
-@pytest.mark.parametrize("op", [W.conv("deep3x3", 1, 48, 9, 72, 3, 1), F32_OPS[1], F32_OPS[4], F32_OPS[5]],
-                         ids=lambda o: o.name)
+STAGING_OPS = [W.conv("deep3x3", 1, 48, 9, 72, 3, 1), F32_OPS[1], F32_OPS[4], F32_OPS[5],
+               W.conv("pw52", 1, 52, 13, 36, 1, 1, 0), W.conv("pw52s2", 1, 52, 17, 36, 1, 2, 0),
+               W.conv("f5c20", 1, 20, 13, 24, 5, 1, 2), W.conv("f7c12s2", 1, 12, 21, 20, 7, 2, 3)]
+
+
+@pytest.mark.parametrize("op", STAGING_OPS, ids=lambda o: o.name)
 def test_direct_staging_paths_match_oracle(op):
-    # every way the direct family reads its operands: registers (per-tap
-    # input offsets kept resident for a fixed 1x1 or 3x3 filter) with vector
-    # or scalar filter loads, LDS chunks prefetched through registers at each
-    # depth (2, 4, 8, 16 elements per thread; a last chunk shorter than CT
-    # where C is not a multiple of it, split channel ranges), and LDS staging
-    # in batches of four or sixteen loads
+    # every way the direct family reads its operands: registers with vector or scalar
+    # filter loads; LDS chunks staged through registers by each loop length, copied by a
+    # plan, by 16 bytes without one or word by word, plane by plane or flat (a last chunk
+    # shorter than CT where C is not a multiple of it, split channel ranges). The copies by
+    # 16 bytes need w at a 16-byte address: those schedules run with w one float off as
+    # well, where its copies go word by word
     x, w = make_inputs(op, "uniform", seed=31)
     ref, a = reference(op, x, w)
     xd, wd, yd = to_device(op, x, w)
+    w_off = torch.empty(wd.numel() + 1, dtype=wd.dtype, device=wd.device)
+    w_off[1:] = wd.reshape(-1)
+    w_off = w_off[1:].reshape(wd.shape)
     by = {}
     for s in L.ct_valid_space(op):
         if s.family == W.FAM_DIRECT_F32:
             by.setdefault(_direct_class(op, s), []).append(s)
     rng = random.Random(5)
-    seen = set()
-    ragged = 0
+    ragged = off = 0
     for cls in sorted(by):
         pool = by[cls]
-        # prefer schedules whose channel chunks do not divide C, then split ones
-        pick = rng.sample(pool, min(3, len(pool)))
-        odd = [s for s in pool if op.c % s.knob[6] and s not in pick]
-        spl = [s for s in pool if s.knob[7] > 1 and s not in pick]
+        # schedules whose channel chunks do not divide C, and split ones, among them
+        pick = rng.sample(pool, min(2, len(pool)))
+        odd = [s for s in pool if op.c % s.knob[DP.CT] and s not in pick]
+        spl = [s for s in pool if s.knob[DP.SPLIT] > 1 and s not in pick]
         pick += rng.sample(odd, min(2, len(odd))) + rng.sample(spl, min(1, len(spl)))
+        aligned_copies = "plan" in cls or "deep" in cls
         for s in pick:
-            tag = "%s %s [%s]" % (op.name, sched_str(s), cls)
-            note(tag)
-            yd.fill_(float("nan"))
-            L.conv2d_run(op, s, xd, wd, yd)
-            split = W.split_of(s)
-            check_close(op, yd.cpu().numpy(), ref, a, tag, split=4 if split > 1 else 1)
-            seen.add(cls)
-            ragged += bool(op.c % s.knob[6]) and cls.startswith("prefetch")
-    print(op.name, "paths:", sorted(seen), "ragged prefetched chunks:", ragged)
+            for wt in (wd, w_off) if aligned_copies else (wd,):
+                tag = "%s %s [%s%s]" % (op.name, sched_str(s), cls, ", w off" if wt is w_off else "")
+                note(tag)
+                yd.fill_(float("nan"))
+                L.conv2d_run(op, s, xd, wt, yd)
+                check_close(op, yd.cpu().numpy(), ref, a, tag, split=4 if W.split_of(s) > 1 else 1)
+                off += wt is w_off
+            ragged += bool(op.c % s.knob[DP.CT])
+    ways = {" ".join(c.split()[3:]) for c in by if c.startswith("lds")}
+    print(op.name, "paths:", sorted(by), "ragged chunks:", ragged, "with w off:", off)
     if op.name == "deep3x3":
-        assert {"regs-fixed", "prefetch-2", "prefetch-4", "prefetch-8", "prefetch-16", "batch4",
-                "batch16"} <= seen
-        assert ragged > 0
+        assert {"regs spec 3", "regs spec 3 scalar-w", "lds spec 3 plan"} <= set(by)
+        assert {"staged-%d" % n for n in (2, 4, 6, 8, 12, 16, 24)} <= ways and ragged > 0
+        assert {"deep %d %d 1" % (i, j) for i in (0, 1) for j in (0, 1)} <= ways and off > 10
+        assert {"copied 0 1", "copied 1 1"} <= ways
+    if op.name == "pw52s2":  # slices that do not fill the rows of threads they take
+        assert {"deep 0 0 0", "deep 1 0 0", "copied 1 0"} <= ways and off > 10
 
 
 # Degenerate shapes: a one-pixel image (only the centre tap of a padded 3x3

@@ -3,11 +3,11 @@ the fp64 oracle, through the C ABI:
 
 * fp32 MFMA schedules with four loader waves (stages 3), with 1, 2 and 4
   reduction groups and with one chunk or several;
-* direct schedules without LDS whose chunks end in an odd channel count while
-  two channels go per step (UNR 2), for 3x3 and 1x1 filters, and the
-  register-bound instances that take one channel per step;
-* the direct generic-filter path (7x7, 5x3 and dilated filters), whose filter
-  rows do not divide into its tap groups;
+* direct schedules without LDS whose channel ranges are no multiple of the load
+  units in flight, for 3x3 and 1x1 filters, with small register tiles (up to
+  four units) and large ones (one or two);
+* direct schedules without LDS for filters whose rows do not divide into tap
+  groups (dilated and 5x3) or that have a ring of rows of their own (7x7);
 * fp32 MFMA schedules whose 16-pixel MFMA columns span two 8-pixel halo rows
   16 words apart, where the halo's channel pitch is 8 (mod 32) instead of 16.
 Every case also runs on integer inputs, where any summation order is exact.
@@ -17,6 +17,7 @@ import random
 import numpy as np
 import pytest
 
+import direct_paths as DP
 from paper_2008_03602_amd import _lib as L, workloads as W
 from gpu_util import check_close, device_ready, make_inputs, note, reference, sched_str, to_device
 
@@ -24,7 +25,7 @@ pytestmark = pytest.mark.gpu
 
 # knob positions (the schedule's documented order)
 F4_WS, F4_TPW, F4_CPC, F4_STAGES = 5, 6, 7, 8
-D_LDS, D_CT, D_UNR, D_MK, D_MW = 5, 6, 8, 3, 4
+D_LDS, D_UNR, D_MK, D_MW = 5, 8, 3, 4
 
 
 @pytest.fixture(scope="module", autouse=True)
@@ -78,22 +79,23 @@ def test_loader_wave_schedules_match_oracle(op):
     _run(op, picks, seed=21)
 
 
-UNR_OPS = [
-    W.conv("unr_3x3", 1, 7, 11, 12, 3, 1),         # C = 7: chunks of 2 and 4 end odd
-    W.conv("unr_3x3s2", 1, 9, 14, 10, 3, 2),
-    W.conv("unr_1x1", 2, 13, 9, 16, 1, 1, 0),
+RING_OPS = [
+    W.conv("ring_3x3", 1, 7, 11, 12, 3, 1),        # 7 channels, 4 and 3 with a split, 2 and 1
+    W.conv("ring_3x3s2", 1, 9, 17, 10, 3, 2),
+    W.conv("ring_1x1", 2, 13, 9, 16, 1, 1, 0),
+    W.conv("ring_1x1s2", 1, 21, 17, 16, 1, 2, 0),  # a ring of four units of four channels, and five more
 ]
 
 
-@pytest.mark.parametrize("op", UNR_OPS, ids=lambda o: o.name)
-def test_direct_two_channel_steps_with_odd_tails_match_oracle(op):
-    pool = [s for s in L.ct_valid_space(op)
-            if s.family == W.FAM_DIRECT_F32 and s.knob[D_LDS] == 0 and s.knob[D_UNR] == 2
-            and (min(s.knob[D_CT], op.c) % 2 == 1 or op.c % s.knob[D_CT] % 2 == 1)]
+@pytest.mark.parametrize("op", RING_OPS, ids=lambda o: o.name)
+def test_direct_register_rings_with_tails_match_oracle(op):
+    pool = [s for s in L.ct_valid_space(op) if s.family == W.FAM_DIRECT_F32 and s.knob[D_LDS] == 0]
     assert pool
     rng = random.Random(5)
-    # small register tiles (two channels per step) and large ones (one)
-    picks = _pick(pool, lambda s: s.knob[D_MK] * s.knob[D_MW] >= 8, 4, rng)
+    # every register tile, with scalar and vector filter loads, whole ranges and split ones
+    key = lambda s: (s.knob[D_MK], s.knob[D_MW], DP.kernel(op, s)[1], s.knob[DP.SPLIT] > 1)
+    picks = _pick(pool, key, 1, rng)
+    assert {DP.kernel(op, s)[1] for s in picks} == {False, True}
     _run(op, picks, seed=22)
 
 

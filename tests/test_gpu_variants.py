@@ -3,6 +3,7 @@ load width or an address range changes, against the fp64 oracle (or, for tensors
 for it, against shifted sums in torch)."""
 import random
 
+import numpy as np
 import pytest
 import torch
 
@@ -142,6 +143,59 @@ def test_depthwise_planes_around_the_32_bit_part_offsets(op, tc, wide):
         L.conv2d_run(op, s, xd, wd, yd)
         # n products of at most 1: both sums err by at most n roundings of at most n * 2^-24
         assert float((yd - ref).abs().max()) <= 2 * n * n * 2.0 ** -24
+
+
+# Infinities and NaN reach the outputs whose taps read them and no others: a window is read
+# past an image's edge into the neighbouring row or plane, tiles and chunks past the tensor.
+SPECIAL_OPS = [
+    _f32("sv3", 2, 5, 6, 7, 9, 3, 3, 1, (1, 1)),
+    _f32("sv3s2", 1, 6, 9, 11, 10, 3, 3, 2, (1, 1)),
+    _f32("sv1", 1, 7, 5, 9, 12, 1, 1, 1, (0, 0)),
+    _f32("sv1s2", 1, 9, 7, 9, 12, 1, 1, 2, (0, 0)),
+    _f32("sv5", 1, 3, 7, 9, 6, 5, 5, 1, (2, 2)),
+    _f32("sv7s2", 1, 3, 13, 11, 6, 7, 7, 2, (3, 3)),
+    _f32("sv4", 1, 3, 7, 10, 6, 4, 4, 1, (1, 1)),
+    _dw("svdw", 2, 5, 6, 9, 3, 3, 1, (1, 1)),
+    _dw("svdw_s2", 1, 5, 9, 12, 3, 3, 2, (1, 1)),
+    W.Op("svbf", 1, 24, 5, 7, 17, 1, 1, dtype=W.DT_BF16, layout=W.LAYOUT_NHWC),
+]
+
+
+@pytest.mark.parametrize("op", SPECIAL_OPS, ids=lambda o: o.name)
+def test_special_values_stay_where_they_are_read(op):
+    bf16 = op.dtype == W.DT_BF16
+    x, w = make_inputs(op, "uniform", seed=48)
+    img = x if not bf16 else x.transpose(0, 3, 1, 2)  # a view: NCHW
+    # the last column of the first row (the next row follows it), the first pixel of a
+    # channel (the row before it ends the plane before), the last pixel of the last channel
+    img[0, 0, 0, -1] = np.nan
+    img[0, 1, 0, 0] = np.inf
+    img[-1, -1, -1, -1] = -np.inf
+    # which taps an output reads: the same layer over marks; a zero weight on a special
+    # value counts (0 * inf is NaN), and there is none
+    assert (w != 0).all()
+    marks = np.zeros_like(x)
+    marks[~np.isfinite(x)] = 1
+    touched, _ = reference(op, marks, np.ones_like(w))
+    ref, a = reference(op, np.where(np.isfinite(x), x, 0).astype(x.dtype), w)
+    nans = np.zeros_like(x)
+    nans[np.isnan(x)] = 1
+    nan_at, _ = reference(op, nans, np.ones_like(w))
+    xd, wd, yd = to_device(op, x, w)
+    space = [s for s in L.ct_valid_space(op) if s.family != W.FAM_IGEMM_F32]
+    by = {}  # one schedule of every kernel, then a sample
+    for s in random.Random(14).sample(space, len(space)):
+        by.setdefault(L.ct_kernel_name(op, s), s)
+    for s in list(by.values()) + random.Random(15).sample(space, min(30, len(space))):
+        tag = "%s %s" % (op.name, sched_str(s))
+        note(tag)
+        yd.fill_(float("nan"))
+        L.conv2d_run(op, s, xd, wd, yd)
+        y = yd.cpu().numpy()
+        assert np.array_equal(np.isfinite(y), touched == 0), tag
+        assert np.isnan(y[nan_at > 0]).all(), tag
+        check_close(op, np.where(touched == 0, y, 0), np.where(touched == 0, ref, 0), np.where(touched == 0, a, 1), tag,
+                    split=4)
 
 
 def _pw(name, n, c, h, w, k, stride=1):

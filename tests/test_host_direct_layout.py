@@ -4,7 +4,10 @@ import os
 import re
 import subprocess
 
-from paper_2008_03602_amd import workloads as W
+import pytest
+
+import direct_paths as DP
+from paper_2008_03602_amd import _lib as L, workloads as W
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2008_03602_amd", "csrc")
@@ -28,18 +31,42 @@ OPS = W.resnet18() + [
 ]
 
 
-def test_every_lds_schedule_stays_inside_its_lds(tmp_path):
-    exe = str(tmp_path / "direct_layout")
+@pytest.fixture(scope="module")
+def driver(tmp_path_factory):
+    tmp = tmp_path_factory.mktemp("direct_layout")
+    exe = str(tmp / "direct_layout")
     cmd = ["g++", "-std=c++17", "-O1", "-g", "-fsanitize=undefined", "-fno-sanitize-recover=all",
            "-I", os.path.join(ROOT, "include"), "-I", CSRC, os.path.join(ROOT, "tests", "direct_layout.cpp"),
            os.path.join(CSRC, "schedule.cpp"), "-o", exe]
     r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     assert r.returncode == 0, r.stdout[-3000:]
-    listing = tmp_path / "ops.txt"
-    listing.write_text("".join(" ".join(str(v) for v in o.as_tuple()) + "\n" for o in OPS))
-    p = subprocess.run([exe, str(listing)], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=300)
-    assert p.returncode == 0, p.stdout[-3000:]
-    rows = [[int(v) for v in re.findall(r"\d+", l)] for l in p.stdout.splitlines() if l.startswith("op ")]
+
+    def run(ops, *args):
+        listing = tmp / "ops.txt"
+        listing.write_text("".join(" ".join(str(v) for v in o.as_tuple()) + "\n" for o in ops))
+        p = subprocess.run([exe, str(listing)] + list(args), stdout=subprocess.PIPE, stderr=subprocess.STDOUT,
+                           text=True, timeout=300)
+        assert p.returncode == 0, p.stdout[-3000:]
+        return p.stdout.splitlines()
+    return run
+
+
+def test_every_lds_schedule_stays_inside_its_lds(driver):
+    lines = driver(OPS)
+    rows = [[int(v) for v in re.findall(r"\d+", l)] for l in lines if l.startswith("op ")]
     assert len(rows) == len(OPS) and all(r[1] > 0 for r in rows)
     # each way a chunk can go is taken
     assert all(sum(r[i] for r in rows) > 1000 for i in (2, 3, 4))
+
+
+@pytest.mark.parametrize("op", OPS[::3] + OPS[-2:], ids=lambda o: o.name)
+def test_the_ways_that_the_gpu_tests_pick_by_are_the_librarys(driver, op):
+    n = 0
+    for line in driver([op], "list"):
+        f = line.split()
+        if f[0].isdigit():
+            n += 1
+            if n % 7 == 0:  # names are asked for one by one
+                s = L.make_schedule(W.FAM_DIRECT_F32, [int(v) for v in f[:9]])
+                assert DP.lds_way(op, s) == (f[9],) + tuple(int(v) for v in f[10:]), line
+    assert n > 100
