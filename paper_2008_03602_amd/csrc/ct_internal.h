@@ -27,9 +27,10 @@ constexpr int kMaxLoadsPerThread = 8;     // register staging bound of the GEMM 
 // Byte offsets of a depthwise block are sums of up to three parts (plane, row, column),
 // each of which may be outside on its own: buffers of at most kPartOob bytes, and kPartOob
 // for a part outside. Any sum with such a part is then past the buffer, and three of them
-// (plus an instruction's immediate) stay below 2^32. The parts are unsigned: three outside
-// exceed the largest int.
-constexpr unsigned kPartOob = 0x3FFFFFF0u;
+// (plus an instruction's immediate) stay below 2^32. Two fit an int; the third is added
+// unsigned.
+constexpr int kPartOob = 0x3FFFFFF0;
+constexpr unsigned part_sum(int two, int third) { return (unsigned)two + (unsigned)third; }
 // fp32 MFMA family, stages 3 (four loader waves): the largest accumulator
 // tile in registers that still leaves room, two waves per SIMD, for the copy
 // plan the loaders keep across the chunk loop (no spills up to here)

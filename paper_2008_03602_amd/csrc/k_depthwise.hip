@@ -96,13 +96,13 @@ depthwise_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, f
   const int oh = bk.oh0 + td.rowg * RPT;  // first output row of the thread
 
   // buffers from the block's first plane (and filter) on
-  const unsigned HW = (unsigned)H * W, OHW = (unsigned)a.OH * a.OW;  // (part sums are unsigned)
+  const int HW = H * W, OHW = a.OH * a.OW;
   const int64_t plane0 = (int64_t)bk.n0 * C + bk.c0, planes = (int64_t)a.N * C - plane0;
   auto range = [](int64_t bytes) { return bytes < kPartOob ? bytes : (int64_t)kPartOob; };
   const float* xb = x + plane0 * HW;
   const __amdgpu_buffer_rsrc_t rx = make_rsrc(xb, range(planes * HW * 4));
   const __amdgpu_buffer_rsrc_t rwt = make_rsrc(w + (int64_t)bk.c0 * R * S, range((int64_t)(C - bk.c0) * R * S * 4));
-  const unsigned wofs = part(live, (unsigned)td.ci * R * S);
+  const int wofs = live ? td.ci * R * S * 4 : kPartOob;
 
   float wv[RC ? RC * RC : 1];
   if constexpr (WIDE && RC != 0) {
@@ -110,7 +110,7 @@ depthwise_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, f
     for (int i = 0; i < RC * RC; ++i) wv[i] = load_or_zero(w, (int64_t)c * RC * RC + i, live);
   } else if constexpr (RC != 0) {
 #pragma unroll
-    for (int r = 0; r < RC; ++r) bload3(rwt, wofs + r * 12u, wv + r * 3);
+    for (int r = 0; r < RC; ++r) bload3(rwt, wofs + r * 12, wv + r * 3);
   }
   float acc[RPT][VEC];
 #pragma unroll
@@ -140,13 +140,13 @@ depthwise_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, f
       const int p0 = qdiv(t, a.inv_plane), rem = t - p0 * plane;
       int hh = qdiv(rem, a.inv_iwt), ww = rem - hh * a.iw_t;
       int ni = qdiv(p0, a.inv_tc), ci = p0 - ni * a.tc;
-      unsigned pofs = ((unsigned)ni * C + ci) * HW;
+      unsigned pofs = (unsigned)(ni * C + ci) * (unsigned)HW;  // (runs past the last plane)
       const int n_left = a.N - bk.n0, c_left = C - bk.c0;
       const int wbase = wave_id() * 64;
       for (int e0 = 0; e0 < total; e0 += a.threads) {
         const int gh = ih_org + hh, gw = iw_org + ww;
         const bool ok = ni < n_left && ci < c_left && (unsigned)gh < (unsigned)H && (unsigned)gw < (unsigned)W;
-        if (e0 + t < total) copy_to_lds(rx, smem + e0 + wbase, part(ok, pofs + (unsigned)gh * W + gw));
+        if (e0 + t < total) copy_to_lds(rx, smem + e0 + wbase, ok ? (pofs + gh * W + gw) * 4 : (unsigned)kPartOob);
         ww += a.st_w;
         const bool k1 = ww >= a.iw_t;
         ww -= k1 ? a.iw_t : 0;
@@ -157,7 +157,7 @@ depthwise_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, f
         const bool k3 = ci >= a.tc;
         ci -= k3 ? a.tc : 0;
         ni += a.st_n + (k3 ? 1 : 0);
-        pofs += a.st_p + (k2 ? HW : 0u) + (k3 ? (unsigned)(C - a.tc) * HW : 0u);
+        pofs += (unsigned)a.st_p + (k2 ? (unsigned)HW : 0u) + (k3 ? (unsigned)(C - a.tc) * (unsigned)HW : 0u);
       }
       wait_copies();
     }
@@ -167,7 +167,7 @@ depthwise_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, f
   // operand (input row `row` of the thread's window rows, column `col`) sources:
   // LDS at (row, column) of the staged tile, or global at row and column offsets
   const float* xs = smem + (td.ni * a.tc + td.ci) * plane + td.rowg * RPT * sh * a.iw_t + td.colg * sw;
-  const unsigned pofs = part(live, ((unsigned)td.ni * C + td.ci) * HW);
+  const int pofs = WIDE ? 0 : (live ? (td.ni * C + td.ci) * HW * 4 : kPartOob);
   const int ih0 = oh * sh - ph;
   if constexpr (WIDE && !LDS) {
     // one output row at a time: planes this large come from HBM, and the rows of a tap are
@@ -193,14 +193,14 @@ depthwise_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, f
     }
   } else if constexpr (RC != 0) {
     constexpr int NIN = (RPT - 1) * STC + RC;  // input rows of the thread's outputs
-    unsigned cofs[VEC][RC];
+    int cofs[VEC][RC];
     if constexpr (!LDS) {
 #pragma unroll
       for (int v = 0; v < VEC; ++v)
 #pragma unroll
         for (int s = 0; s < RC; ++s) {
           const int gw = (bk.ow0 + td.colg + v * a.cols) * STC - 1 + s;
-          cofs[v][s] = part((unsigned)gw < (unsigned)W, gw);
+          cofs[v][s] = (unsigned)gw < (unsigned)W ? gw * 4 : kPartOob;
         }
     }
 #pragma unroll
@@ -214,11 +214,11 @@ depthwise_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, f
           for (int s = 0; s < RC; ++s) xv[v][s] = xr[v * a.cols * STC + s];
       } else {
         const int gh = ih0 + i;
-        const unsigned rofs = pofs + part((unsigned)gh < (unsigned)H, (unsigned)gh * W);
+        const int rofs = pofs + ((unsigned)gh < (unsigned)H ? gh * W * 4 : kPartOob);
 #pragma unroll
         for (int v = 0; v < VEC; ++v)
 #pragma unroll
-          for (int s = 0; s < RC; ++s) xv[v][s] = bload1(rx, rofs + cofs[v][s]);
+          for (int s = 0; s < RC; ++s) xv[v][s] = bload1(rx, part_sum(rofs, cofs[v][s]));
       }
       // input row i feeds output row u through filter row i - u * STC; every output
       // adds its terms in (r, s) order
@@ -239,12 +239,12 @@ depthwise_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, f
         if constexpr (WIDE)
           wt = live ? w[((int64_t)c * R + r) * S + s] : 0.f;
         else
-          wt = bload1(rwt, wofs + 4u * ((unsigned)r * S + s));
+          wt = bload1(rwt, wofs + (r * S + s) * 4);
 #pragma unroll
         for (int u = 0; u < RPT; ++u) {
           const int gh = ih0 + u * sh + r * dh;
           const bool hok = (unsigned)gh < (unsigned)H;
-          const unsigned rofs = pofs + part(hok, (unsigned)gh * W);
+          const int rofs = pofs + (hok ? gh * W * 4 : kPartOob);
 #pragma unroll
           for (int v = 0; v < VEC; ++v) {
             const int gw = (bk.ow0 + td.colg + v * a.cols) * sw - pw + s * dw;
@@ -252,7 +252,7 @@ depthwise_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, f
             if constexpr (LDS)
               xv = xs[(u * sh + r * dh) * a.iw_t + v * a.cols * sw + s * dw];
             else
-              xv = bload1(rx, rofs + part((unsigned)gw < (unsigned)W, gw));
+              xv = bload1(rx, part_sum(rofs, (unsigned)gw < (unsigned)W ? gw * 4 : kPartOob));
             acc[u][v] = fmaf(wt, xv, acc[u][v]);
           }
         }
@@ -274,14 +274,14 @@ depthwise_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, f
     }
   } else {
     const __amdgpu_buffer_rsrc_t ry = make_rsrc(y + plane0 * OHW, range(planes * OHW * 4));
-    const unsigned yofs = part(live, ((unsigned)td.ni * C + td.ci) * OHW);
+    const int yofs = live ? (td.ni * C + td.ci) * OHW * 4 : kPartOob;
 #pragma unroll
     for (int u = 0; u < RPT; ++u) {
-      const unsigned rofs = yofs + part(oh + u < a.OH, (unsigned)(oh + u) * a.OW);
+      const int rofs = yofs + (oh + u < a.OH ? (oh + u) * a.OW * 4 : kPartOob);
 #pragma unroll
       for (int v = 0; v < VEC; ++v) {
         const int ow = bk.ow0 + td.colg + v * a.cols;
-        bstore1(ry, rofs + part(ow < a.OW, ow), acc[u][v]);
+        bstore1(ry, part_sum(rofs, ow < a.OW ? ow * 4 : kPartOob), acc[u][v]);
       }
     }
   }

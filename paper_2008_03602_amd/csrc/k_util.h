@@ -69,10 +69,6 @@ __device__ __forceinline__ void bstore1(__amdgpu_buffer_rsrc_t r, unsigned off, 
   __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, (int)off, 0, 0);
 }
 
-// An offset part (kPartOob) of `words` words: below kPartOob bytes where it is inside,
-// anything elsewhere.
-constexpr unsigned part(bool inside, unsigned words) { return inside ? 4u * words : kPartOob; }
-
 typedef __attribute__((address_space(3))) void lds_void_t;
 // One wave instruction: lane i copies the word at byte offset off of r to
 // lds[i] (an inactive lane copies nothing), without a trip through registers.

@@ -1,6 +1,6 @@
 """Byte offsets of the kernels' buffer accesses: an offset may be a sum of parts of which
 each is outside the image on its own, and a multi-word access goes on past one. Such sums
-exceed the largest int, so their types have to be unsigned. Constant evaluation refuses a
+exceed the largest int and have to be made unsigned. Constant evaluation refuses a
 signed overflow, which makes the compiler the check (a syntax check of the host side)."""
 import os
 import subprocess
@@ -10,7 +10,7 @@ from paper_2008_03602_amd import build as B
 UNIT = r"""
 #include "k_util.h"
 // a dead thread, a row outside and a column outside at once, plus the immediate
-constexpr auto three = ct::kPartOob + ct::kPartOob + ct::kPartOob;
+constexpr auto three = ct::part_sum(ct::kPartOob + ct::kPartOob, ct::kPartOob);
 static_assert(three == 0xBFFFFFD0 && three + 4095 > three, "three parts outside stay below 2^32");
 // a row and a column outside, and the later words of a window that starts outside
 constexpr auto two = ct::kOob + ct::kOob;
@@ -18,11 +18,10 @@ static_assert(two == 0xFFFFFFE0, "");
 constexpr auto window = ct::kOob + 16 + 16 + 4;
 static_assert(window > ct::kOob, "");
 // one part outside sends any sum with parts inside past the largest buffer, in any order
-constexpr unsigned last = ct::kPartOob / 4 - 1;
-static_assert(ct::part(true, last) < ct::kPartOob, "");
-static_assert(ct::part(false, last) + ct::part(true, last) + ct::part(true, last) >= ct::kPartOob, "");
-static_assert(ct::part(false, 0) + ct::part(false, 0) + ct::part(true, last) >= ct::kPartOob, "");
-static_assert(ct::part(false, 0u - 1) == ct::kPartOob, "what an outside part would have been does not matter");
+constexpr int last = ct::kPartOob - 4;
+static_assert(ct::part_sum(ct::kPartOob + 0, 0) >= ct::kPartOob, "");
+static_assert(ct::part_sum(last + ct::kPartOob, last) >= ct::kPartOob, "");
+static_assert(ct::part_sum(last + last, ct::kPartOob) >= ct::kPartOob, "");
 """
 
 
