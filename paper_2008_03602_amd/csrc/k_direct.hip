@@ -39,7 +39,6 @@ int launch_direct_f32(const OpX& x, const ct_schedule& s, const Geom& g, const v
   a.deep_x = a.deep_w = a.vec_w = 0;
   a.inv_plane = a.inv_pitch = a.inv_ks = a.inv_wpc = a.inv_wq = 0.f;
   if (s.knob[LDS]) {
-    
     a.inv_plane = 1.0f / (float)(a.ih_t * a.pitch);
     a.inv_pitch = 1.0f / (float)a.pitch;
     a.inv_ks = 1.0f / (float)a.ks;

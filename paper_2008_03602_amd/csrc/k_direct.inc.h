@@ -39,9 +39,9 @@
 //     registers are reloaded for a later one right after its multiply-adds.
 // Measured on 80 sampled schedules of each ResNet-18 b1 layer and of three
 // ragged ones (3x3, 5x5, 7x7), against strided columns, single-word reads and
-// one step of loads at a time, summed: 94.6 to 59.6 ms on the whole GPU, 188.7
-// to 128.7 ms on a quarter; a 5x5 layer of 37 channels (4 x 45 x 51 pixels, its
-// best schedule) 52.1 to 35.1 us.
+// one step of loads at a time, summed: 99.4 to 59.5 ms on the whole GPU, 182.4
+// to 118.9 ms on a quarter; a 5x5 layer of 37 channels (4 x 45 x 51 pixels, its
+// best schedule) 52.1 to 33.9 us.
 //
 // Global reads are raw buffer loads with 32-bit offsets: an element outside
 // the tensor (padding, a tile past the edge) gets an offset past the buffer,
@@ -315,17 +315,17 @@ direct_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, floa
       return j < a.ct * RS && i < min(MK, k_left) ? (unsigned)(i * C * RS + j) * 4 : kOob;
     };
     // Element e of the filter region (wt words, whole rows of `threads`) and
-    // of the halo region goes to LDS word e of that region. Where both take at
-    // most kMaxNs elements per thread, they go through registers: the next
+    // of the halo region goes to LDS word e of that region. Where both together
+    // take at most kMaxNs elements per thread, they go through registers: the next
     // chunk's loads are in flight during this chunk's MACs, so a block pays
     // one memory round trip per chunk only once. An element's offset depends
     // on the chunk only through its first channel cc, which moves the buffer's
     // base instead: the offsets are computed once, and a chunk's loads and
     // stores take no address arithmetic on lanes and no lane masks (both
     // regions are padded to whole rows of the block's threads; an element past
-    // its region is loaded as 0). Channels of a last, partial chunk past nc stage values that the
-    // MACs never read. kMaxNs is what fits beside the accumulators and the
-    // units in flight.
+    // its region is loaded as 0). Channels of a last, partial chunk past nc
+    // stage values that the MACs never read. kMaxNs is what fits beside the
+    // accumulators and the units in flight (direct_regs).
     const int xt = a.ct * plane, wt = a.wt;
     auto rows = [&](const int words) { return __builtin_amdgcn_readfirstlane((words + a.threads - 1) / a.threads); };
     const int nsx = rows(xt), nsw = rows(wt), nst = nsw + nsx;

@@ -35,9 +35,9 @@
 //     no bounds branch, no select, no address arithmetic per load.
 // Measured, 3076 sampled schedules of the MobileNet-v2 b16 pointwise layers and
 // a ragged one, summed, against one chunk through registers (LDS = 1) and two
-// chunks of fragments with clamped addresses (LDS = 0): 39.3 to 30.0 ms on the
-// whole GPU, 69.3 to 47.6 ms on a quarter (LDS = 1: 23.1 to 16.0 and 41.4 to
-// 24.6; LDS = 0: 16.2 to 14.0 and 27.9 to 23.0). Channels as the matrix
+// chunks of fragments with clamped addresses (LDS = 0): 37.5 to 28.0 ms on the
+// whole GPU, 65.9 to 44.5 ms on a quarter (LDS = 1: 22.6 to 15.2 and 40.7 to
+// 23.7; LDS = 0: 14.9 to 12.9 and 25.3 to 20.9). Channels as the matrix
 // instruction's rows, for 16-byte stores, lost: 30 % slower at K = 96 and up,
 // where a store then touches 16 pixels instead of 4.
 #include <hip/hip_runtime.h>

@@ -301,7 +301,9 @@ igemm_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, float
     const float* Xs = smem + stage * stage_floats;
     const float* As = Xs + a.xs_pad;
     if constexpr (RC != 0) {
-      constexpr int kUnrollSteps = RC == 1 ? 4 : 1;  // a 1x1 filter has one tap per step
+      // a 1x1 filter has one tap per step (asked for: the compiler leaves this loop of a
+      // runtime length as it is, a read, a wait and the products of one step at a time)
+      constexpr int kUnrollSteps = RC == 1 ? 4 : 1;
 #pragma unroll kUnrollSteps
       for (int ii = 0; ii < n_i; ++ii) {
         const float* ap = As + (i_begin + ii) * astep;
