@@ -422,12 +422,12 @@ direct_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, floa
     const int gq = a.ks / 4, ng = min(a.tk / MK, (K - k0 + MK - 1) / MK);
     auto quad = [&](const int q) {  // byte offset of 16-byte quad q of a group's slice
       const int rq = wrow / 4, i = qdiv(q, a.inv_wq), j = q - i * rq;
-      return i < MK ? ((unsigned)i * C * RS + 4 * j) * 4 : kOob;
+      return i < MK ? ((unsigned)i * C * RS + 4 * j) * 4 : kOobQuad;
     };
     auto flat_quad = [&](const int e) {  // and of the whole filter region
       const int kg = qdiv(e, 4.f * a.inv_ks);
       const unsigned o = quad(e - kg * gq);
-      return e < ng * gq && o != kOob ? o + (unsigned)kg * MK * C * RS * 4 : kOob;
+      return e < ng * gq && o != kOobQuad ? o + (unsigned)kg * MK * C * RS * 4 : kOobQuad;
     };
     if constexpr (DEEP) {
       npw = rows(ng * gq);

@@ -188,7 +188,7 @@ igemm_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, float
         const int hh = qdiv(rem, a.inv_ru), col = (rem - hh * ru) * vh;
         const int gh = ih0 + hh, gw = iw0 - a.hshift + col;
         const bool ok = c < cl && rem < rows_u && (unsigned)gh < (unsigned)a.H && (unsigned)gw < (unsigned)a.W;
-        h_off[i] = ok ? (c * HW + gh * a.W + gw) * 4 : kOob;
+        h_off[i] = ok ? (c * HW + gh * a.W + gw) * 4 : (int)kOobQuad;
         // advance by T units: (c, rem) += (h_dc, h_drem) with a carry
         rem += a.h_drem;
         const int cr = rem >= pu;
@@ -218,7 +218,7 @@ igemm_f32_kernel(const float* __restrict__ x, const float* __restrict__ w, float
       if (j < n_filt_w) {
         const int s0 = jw >= seg_len ? min(seg * seg_len, jw - seg_len) : 0;
         const int jj = s0 + lane * vf;
-        f_off[j] = jj < cl * RS ? (m * a.kred + jj) * 4 : kOob;
+        f_off[j] = jj < cl * RS ? (m * a.kred + jj) * 4 : (int)kOobQuad;
         f_dst[j] = m * lda + s0;
         seg += dseg;
         m += dm;

@@ -22,9 +22,12 @@ __device__ __forceinline__ T load_or_zero(const T* __restrict__ p, int64_t idx, 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, int64_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, (int)bytes, 0x00020000);
 }
-// Byte offset beyond every buffer of the fp32 families: reads as 0. Offsets are unsigned,
-// since the words after it, or a second part outside, pass the largest int.
-constexpr unsigned kOob = 0x7FFFFFF0u;
+// Byte offset beyond every buffer of the fp32 families, which hold fewer than 2^31 bytes in
+// whole words: reads as 0. Offsets are unsigned, since the words after it, or a second part
+// outside, pass the largest int.
+constexpr unsigned kOob = 0x7FFFFFFCu;
+// The same at a 16-byte offset, for copies of that width and where nothing is added.
+constexpr unsigned kOobQuad = 0xFFFFFFF0u;
 
 // One word at byte offset off of r (0 past the buffer's range).
 __device__ __forceinline__ float bload1(__amdgpu_buffer_rsrc_t r, unsigned off) {

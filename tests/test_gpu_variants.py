@@ -198,6 +198,30 @@ def test_special_values_stay_where_they_are_read(op):
                     split=4)
 
 
+def test_padding_of_an_image_that_ends_just_before_2_gib():
+    # x of 2^29 - 2 words: what lies outside the image must not read its last words, the only
+    # ones that are not 0
+    op = _f32("end", 1, 2, 18705, 14351, 1, 3, 3, 1, (1, 1))
+    xd = torch.zeros(op.x_shape(), device="cuda")
+    assert xd.numel() == 2 ** 29 - 2
+    xd.view(-1)[-2:] = 1e6
+    wd = torch.ones(op.w_shape(), device="cuda")
+    yd = torch.empty(op.y_shape(), device="cuda")
+    ref = torch.zeros(op.y_shape(), device="cuda")
+    ref[0, 0, -2:, -3] = 1e6
+    ref[0, 0, -2:, -2:] = 2e6
+    for fam, knobs in ((W.FAM_DIRECT_F32, (8, 32, 4, 4, 4, 1, 2, 1, 1)),
+                       (W.FAM_DIRECT_F32, (8, 32, 4, 4, 4, 0, 2, 1, 1)),
+                       (W.FAM_DIRECT_F32, (14, 16, 4, 1, 1, 1, 1, 1, 1)),
+                       (W.FAM_IGEMM_F32, (16, 1, 4, 1, 4, 1, 64, 2, 1, 1))):
+        s = L.make_schedule(fam, knobs)
+        assert L.ct_validate(op, s) == L.S_OK
+        note("end " + sched_str(s))
+        yd.fill_(float("nan"))
+        L.conv2d_run(op, s, xd, wd, yd)
+        assert torch.equal(yd, ref), sched_str(s)
+
+
 def _pw(name, n, c, h, w, k, stride=1):
     return W.Op(name, n, c, h, w, k, 1, 1, stride, stride, 0, 0, 1, 1, 1, W.DT_BF16, W.LAYOUT_NHWC)
 

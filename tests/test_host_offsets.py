@@ -14,7 +14,10 @@ constexpr auto three = ct::part_sum(ct::kPartOob + ct::kPartOob, ct::kPartOob);
 static_assert(three == 0xBFFFFFD0 && three + 4095 > three, "three parts outside stay below 2^32");
 // a row and a column outside, and the later words of a window that starts outside
 constexpr auto two = ct::kOob + ct::kOob;
-static_assert(two == 0xFFFFFFE0, "");
+static_assert(two == 0xFFFFFFF8, "");
+// past the largest tensor, which holds fewer than 2^31 bytes in whole words
+static_assert(ct::kOob >= 0x7FFFFFFF / 4 * 4 && ct::kOob % 4 == 0, "");
+static_assert(ct::kOobQuad >= 0x7FFFFFFF / 4 * 4 && ct::kOobQuad % 16 == 0, "");
 constexpr auto window = ct::kOob + 16 + 16 + 4;
 static_assert(window > ct::kOob, "");
 // one part outside sends any sum with parts inside past the largest buffer, in any order
